@@ -13,6 +13,7 @@ typedef _Float16 f16;
 typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));   // in a caller's buffer: aligned like a float
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
@@ -60,6 +61,20 @@ __device__ __forceinline__ void mfma32(f32x16 &acc, const f32x4 &a, const f32x4 
   acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[1], b[1], acc, 0, 0, 0);
   acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[2], b[2], acc, 0, 0, 0);
   acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[3], b[3], acc, 0, 0, 0);
+}
+
+// The 16x16 forms: lane l supplies row l % 16 and k-slot group l / 16 (fp16: one
+// v_mfma_f32_16x16x32_f16, k-extent 32; f32: four v_mfma_f32_16x16x4_f32, k-extent
+// 16 in total); register r of lane l of the accumulator holds row 4 (l / 16) + r,
+// column l % 16.
+__device__ __forceinline__ void mfma16(f32x4 &acc, const f16x8 &a, const f16x8 &b) {
+  acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, acc, 0, 0, 0);
+}
+__device__ __forceinline__ void mfma16(f32x4 &acc, const f32x4 &a, const f32x4 &b) {
+  acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[0], b[0], acc, 0, 0, 0);
+  acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[1], b[1], acc, 0, 0, 0);
+  acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[2], b[2], acc, 0, 0, 0);
+  acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[3], b[3], acc, 0, 0, 0);
 }
 
 // Accumulator layout of a 32x32 MFMA tile: register r of lane l holds

@@ -85,14 +85,11 @@ hipError_t launch_gemm(int mode, int epi, const void *A, const void *W, void *C,
 // The same with an explicit tile configuration (index into the GEMM tile
 // table) and number of K splits (> 1 only with EPI_PARTIAL, partial sums
 // c_plane elements apart); used for tuning. Returns hipErrorInvalidValue if
-// the tile does not fit the shape. xcd: placement of the tiles on the eight
-// XCDs, 100 xa + 10 xb + xc with xa x xb x xc = 8 groups of M tiles, N tiles
-// and K splits (each XCD reads only its groups' operands); 0, or a placement
-// that does not divide the grid: workgroup order by N tile.
+// the tile does not fit the shape.
 hipError_t launch_gemm_tile(int mode, int epi, int tile, int splits, const void *A, const void *W,
                             void *C, size_t c_plane, int M, int N, int K, int ldc, float scale,
                             float out_scale, const QkvEpi *qe, hipStream_t s,
-                            const float *col_scale = nullptr, const float *bias = nullptr, int xcd = 0);
+                            const float *col_scale = nullptr, const float *bias = nullptr);
 int gemm_num_tiles();
 
 // Per-row RMSNorm: out[r, :] = x[r, :] / sqrt(mean(x[r,:]^2) + eps) * g with
