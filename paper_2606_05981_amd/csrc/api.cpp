@@ -505,9 +505,10 @@ struct PrefixCtx {
   bool record;
 };
 
-// Runs layers [l0, l1) on the fp32 residual stream `h` (T rows).
+// Runs layers [l0, l1) on the fp32 residual stream `h` (T rows). The first
+// layer's attention norm is the caller's (launch_first_norm into wk.xn).
 hipError_t run_layers(mte_encoder *e, const Work &wk, float *h, const int32_t *cu, int batch, int T, int l0,
-                      int l1, bool first_norm_done, int *pending, hipStream_t s,
+                      int l1, int *pending, hipStream_t s,
                       const PrefixCtx *pre = nullptr) {
   const mte_config &c = e->cfg;
   const int D = c.hidden, d = c.head_dim, Hq = c.n_q_heads, Hkv = c.n_kv_heads, F = c.ffn;
@@ -522,7 +523,7 @@ hipError_t run_layers(mte_encoder *e, const Work &wk, float *h, const int32_t *c
 #define MTE_TRY(x) do { err = (x); if (err != hipSuccess) return err; } while (0)
   for (int l = l0; l < l1; ++l) {
     const LayerW &W = e->layers[l];
-    if (!(l == l0 && first_norm_done))
+    if (l > l0)
       MTE_TRY(launch_rmsnorm(FMT_F32, af, h, np ? h : nullptr, np ? ws : nullptr, np, W.attn_norm, wk.xn, T,
                              D, c.rms_eps, s));
     int sp = 0;
@@ -618,13 +619,11 @@ hipError_t encode_on(mte_encoder *e, const Work &wk, const void *embeds, const i
   if (c.n_layers == 0)
     return launch_rmsnorm(in_fmt(c.dtype), out_fmt, embeds, nullptr, nullptr, 0, e->final_norm, out_hidden, T,
                           c.hidden, c.rms_eps, stream);
-  hipError_t err = launch_rope_table(pos_thw, T, c.head_dim / 2, e->rope, wk.rcos, wk.rsin, stream);
   // Layer 0's attention norm also seeds the fp32 residual stream from the embeddings.
-  if (err == hipSuccess)
-    err = launch_rmsnorm(in_fmt(c.dtype), e->act_fmt, embeds, wk.h, nullptr, 0, e->layers[0].attn_norm, wk.xn,
-                         T, c.hidden, c.rms_eps, stream);
+  hipError_t err = launch_first_norm(in_fmt(c.dtype), e->act_fmt, embeds, wk.h, e->layers[0].attn_norm, wk.xn, T,
+                                     c.hidden, c.rms_eps, pos_thw, c.head_dim / 2, e->rope, wk.rcos, wk.rsin, stream);
   int np = 0;
-  if (err == hipSuccess) err = run_layers(e, wk, wk.h, cu, batch, T, 0, c.n_layers, true, &np, stream);
+  if (err == hipSuccess) err = run_layers(e, wk, wk.h, cu, batch, T, 0, c.n_layers, &np, stream);
   if (err == hipSuccess)
     err = launch_rmsnorm(FMT_F32, out_fmt, wk.h, nullptr, np ? wk.ws : nullptr, np, e->final_norm, out_hidden, T,
                          c.hidden, c.rms_eps, stream);
@@ -723,12 +722,18 @@ int mte_encode_layers(mte_encoder *e, const float *h_in, const int32_t *pos_thw,
   for (int i = 0; i < batch; ++i) cu[i + 1] = cu[i] + seq_lens[i];
   DeviceGuard g(e->device);
   hipError_t err = hipSuccess;
-  if (h_out != h_in) err = hipMemcpyAsync(h_out, h_in, bytes, hipMemcpyDeviceToDevice, stream);
-  if (err == hipSuccess)
-    err = launch_rope_table(pos_thw, T, e->cfg.head_dim / 2, e->rope, e->w.rcos, e->w.rsin, stream);
   int np = 0;
-  if (err == hipSuccess)
-    err = run_layers(e, e->w, h_out, cu.data(), batch, T, layer_begin, layer_end, false, &np, stream);
+  if (layer_begin == layer_end) {
+    if (h_out != h_in) err = hipMemcpyAsync(h_out, h_in, bytes, hipMemcpyDeviceToDevice, stream);
+  } else {
+    // The first norm reads the residual stream anyway, so it also writes h_out
+    // (a copy of its own took 8 us of a 1536-row layer's 207, 30 us at 10240 rows).
+    err = launch_first_norm(FMT_F32, e->act_fmt, h_in, h_out != h_in ? h_out : nullptr,
+                            e->layers[layer_begin].attn_norm, e->w.xn, T, e->cfg.hidden, e->cfg.rms_eps, pos_thw,
+                            e->cfg.head_dim / 2, e->rope, e->w.rcos, e->w.rsin, stream);
+    if (err == hipSuccess)
+      err = run_layers(e, e->w, h_out, cu.data(), batch, T, layer_begin, layer_end, &np, stream);
+  }
   if (err == hipSuccess && np) err = launch_resid_add(h_out, e->w.ws, np, T, e->cfg.hidden, stream);
   return err == hipSuccess ? MTE_OK : MTE_E_HIP;
 }
@@ -786,13 +791,12 @@ int mte_encode_prefixed(mte_encoder *e, const void *prefix_embeds, const int32_t
   {
     std::vector<int32_t> cu{0, prefix_len};
     const PrefixCtx rec{e->pkv, e->pkv_stride, prefix_len, true};
-    err = launch_rope_table(prefix_pos, prefix_len, c.head_dim / 2, e->rope, e->w.rcos, e->w.rsin, stream);
-    if (err == hipSuccess)
-      err = launch_rmsnorm(in_fmt(c.dtype), e->act_fmt, prefix_embeds, e->w.h, nullptr, 0, e->layers[0].attn_norm,
-                           e->w.xn, prefix_len, c.hidden, c.rms_eps, stream);
+    err = launch_first_norm(in_fmt(c.dtype), e->act_fmt, prefix_embeds, e->w.h, e->layers[0].attn_norm, e->w.xn,
+                            prefix_len, c.hidden, c.rms_eps, prefix_pos, c.head_dim / 2, e->rope, e->w.rcos,
+                            e->w.rsin, stream);
     int np = 0;
     if (err == hipSuccess)
-      err = run_layers(e, e->w, e->w.h, cu.data(), 1, prefix_len, 0, c.n_layers, true, &np, stream, &rec);
+      err = run_layers(e, e->w, e->w.h, cu.data(), 1, prefix_len, 0, c.n_layers, &np, stream, &rec);
     if (err == hipSuccess)
       err = launch_rmsnorm(FMT_F32, out_fmt, e->w.h, nullptr, np ? e->w.ws : nullptr, np, e->final_norm, out_prefix,
                            prefix_len, c.hidden, c.rms_eps, stream);
@@ -802,13 +806,11 @@ int mte_encode_prefixed(mte_encoder *e, const void *prefix_embeds, const int32_t
     std::vector<int32_t> cu(batch + 1, 0);
     for (int i = 0; i < batch; ++i) cu[i + 1] = cu[i] + seq_lens[i];
     const PrefixCtx use{e->pkv, e->pkv_stride, prefix_len, false};
-    err = launch_rope_table(pos_thw, T, c.head_dim / 2, e->rope, e->w.rcos, e->w.rsin, stream);
-    if (err == hipSuccess)
-      err = launch_rmsnorm(in_fmt(c.dtype), e->act_fmt, embeds, e->w.h, nullptr, 0, e->layers[0].attn_norm, e->w.xn,
-                           T, c.hidden, c.rms_eps, stream);
+    err = launch_first_norm(in_fmt(c.dtype), e->act_fmt, embeds, e->w.h, e->layers[0].attn_norm, e->w.xn, T, c.hidden,
+                            c.rms_eps, pos_thw, c.head_dim / 2, e->rope, e->w.rcos, e->w.rsin, stream);
     int np = 0;
     if (err == hipSuccess)
-      err = run_layers(e, e->w, e->w.h, cu.data(), batch, T, 0, c.n_layers, true, &np, stream, &use);
+      err = run_layers(e, e->w, e->w.h, cu.data(), batch, T, 0, c.n_layers, &np, stream, &use);
     if (err == hipSuccess)
       err = launch_rmsnorm(FMT_F32, out_fmt, e->w.h, nullptr, np ? e->w.ws : nullptr, np, e->final_norm, out_hidden,
                            T, c.hidden, c.rms_eps, stream);

@@ -103,6 +103,18 @@ hipError_t launch_rmsnorm(int in_fmt, int out_fmt, const void *in, float *copy_t
                           int nparts, const float *g, void *out, int rows, int D, float eps,
                           hipStream_t s);
 
+struct RopeParams {
+  double inv_freq[64];       // theta^(-2j/d) for pair j
+  uint8_t axis[64];          // position axis (0 t, 1 h, 2 w) of pair j
+};
+
+// The two kernels that open a forward, in one launch: launch_rmsnorm without
+// partial sums (out_fmt FMT_F32 or FMT_F16), and launch_rope_table of the
+// `rows` tokens.
+hipError_t launch_first_norm(int in_fmt, int out_fmt, const void *in, float *copy_to, const float *g, void *out,
+                             int rows, int D, float eps, const int32_t *pos_thw, int half, const RopeParams &rp,
+                             float *rcos, float *rsin, hipStream_t s);
+
 // h[rows, D] += parts[0] + ... + parts[nparts-1] (float partial sums, rows*D
 // elements apart, in that order). D a multiple of 4.
 hipError_t launch_resid_add(float *h, const float *parts, int nparts, int rows, int D, hipStream_t s);
@@ -113,11 +125,6 @@ hipError_t launch_resid_add(float *h, const float *parts, int nparts, int rows, 
 // FMT_F16 [rows, F].
 hipError_t launch_swiglu_parts(int out_fmt, const float *parts, int nparts, int rows, int F, void *out,
                                float out_scale, hipStream_t s);
-
-struct RopeParams {
-  double inv_freq[64];       // theta^(-2j/d) for pair j
-  uint8_t axis[64];          // position axis (0 t, 1 h, 2 w) of pair j
-};
 
 // Rotary table of T tokens: rcos / rsin [T, half] = cos / sin of
 // pos_thw[axis(j)][t] * inv_freq[j] (float64 angle and sincos, rounded).

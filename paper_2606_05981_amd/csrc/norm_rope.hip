@@ -8,6 +8,44 @@
 
 namespace mte {
 
+// ---------------------------------------------------- rotary table
+// cos / sin of the rotation angle of every (token, pair): pair j of token
+// t turns by pos[axis(j)][t] * inv_freq[j]; the angle and its sincos are
+// evaluated in float64 and rounded to fp32. Built once per forward and
+// shared by the q and k heads of all layers.
+struct RopeJob {
+  const int32_t *pos;   // [3, T]
+  int T, half;
+  int blocks;           // 256-entry blocks of the table
+  RopeParams rp;
+  float *rcos, *rsin;   // [T, half]
+};
+
+__device__ __forceinline__ void rope_block(const RopeJob &r, int block) {
+  const size_t i = (size_t)block * 256 + threadIdx.x;
+  if (i >= (size_t)r.T * r.half) return;
+  const int tok = (int)(i / r.half), j = (int)(i % r.half);
+  const double ang = (double)r.pos[(size_t)r.rp.axis[j] * r.T + tok] * r.rp.inv_freq[j];
+  double sv, cv;
+  sincos(ang, &sv, &cv);
+  r.rcos[i] = (float)cv;
+  r.rsin[i] = (float)sv;
+}
+
+static RopeJob rope_job(const int32_t *pos_thw, int T, int half, const RopeParams &rp, float *rcos, float *rsin) {
+  return RopeJob{pos_thw, T, half, (int)(((size_t)T * half + 255) / 256), rp, rcos, rsin};
+}
+
+__global__ __launch_bounds__(256) void k_rope_table(RopeJob r) { rope_block(r, blockIdx.x); }
+
+hipError_t launch_rope_table(const int32_t *pos_thw, int T, int half, const RopeParams &rp, float *rcos,
+                             float *rsin, hipStream_t s) {
+  if ((size_t)T * half == 0) return hipSuccess;
+  const RopeJob r = rope_job(pos_thw, T, half, rp, rcos, rsin);
+  hipLaunchKernelGGL(k_rope_table, dim3(r.blocks), dim3(256), 0, s, r);
+  return hipGetLastError();
+}
+
 // ------------------------------------------------------------- RMSNorm
 // out = x / sqrt(mean(x^2) + eps) * g, one 256-thread block per row, where
 // x = in + the np partial sums parts[0..np) (pitch pstride elements), added
@@ -70,48 +108,75 @@ static void rmsnorm_out(int out_fmt, dim3 grid, const TI *in, float *copy_to, co
     hipLaunchKernelGGL((k_rmsnorm<TI, FMT_F16>), grid, dim3(256), 0, s, in, copy_to, pt, g, out, D, eps);
 }
 
-// Register-resident variant for D a multiple of 1024 (D <= 4096): every
-// thread owns NV groups of 4 consecutive values, read once with 16-byte (or
-// 8-byte bf16) loads and written with vector stores.
-template <typename TI, int OUT_FMT, int NV>
+// Register-resident variant: every thread owns NV groups of VW consecutive
+// values, read once with vector loads and written with vector stores. VW = 4
+// for D a multiple of 1024, else 2 or 1 (a multiple of 512 or 256, e.g. the
+// 256-wide fp32 decoder: with the loop over partial sums of the general kernel,
+// a load latency per split and pass, its 32-row norm of 8 partial sums took
+// 4.9 us). ROPE: the first r.blocks blocks of the grid build the batch's rotary
+// table instead (one launch for the two kernels that open a forward; neither
+// reads what the other writes).
+template <typename TI, int VW> struct VecOf;
+template <> struct VecOf<float, 4> { typedef f32x4 type; };
+template <> struct VecOf<float, 2> { typedef float type __attribute__((ext_vector_type(2))); };
+template <> struct VecOf<float, 1> { typedef float type __attribute__((ext_vector_type(1))); };
+template <> struct VecOf<bf16, 4> { typedef bf16x4 type; };
+template <> struct VecOf<bf16, 2> { typedef bf16 type __attribute__((ext_vector_type(2))); };
+template <> struct VecOf<bf16, 1> { typedef bf16 type __attribute__((ext_vector_type(1))); };
+template <> struct VecOf<f16, 4> { typedef f16x4 type; };
+template <> struct VecOf<f16, 2> { typedef f16 type __attribute__((ext_vector_type(2))); };
+template <> struct VecOf<f16, 1> { typedef f16 type __attribute__((ext_vector_type(1))); };
+struct NoRope {};
+
+template <typename TI, int OUT_FMT, int VW, int NV, bool ROPE>
 __global__ __launch_bounds__(256) void k_rmsnorm_vec(const TI *in, float *copy_to, Parts pt,
                                                      const float *__restrict__ gain, void *__restrict__ out,
-                                                     int D, float eps) {
+                                                     int D, float eps,
+                                                     typename std::conditional<ROPE, RopeJob, NoRope>::type r) {
+  typedef typename VecOf<float, VW>::type fv;
+  // in, copy_to and out may be a caller's buffers: aligned like one element
+  typedef fv fvu __attribute__((aligned(4)));
+  typedef typename VecOf<TI, VW>::type tivu __attribute__((aligned(sizeof(TI))));
+  int row = blockIdx.x;
+  if constexpr (ROPE) {
+    if (row < r.blocks) {
+      rope_block(r, row);
+      return;
+    }
+    row -= r.blocks;
+  }
   __shared__ float red[4];
-  const int row = blockIdx.x, tid = threadIdx.x;
+  const int tid = threadIdx.x;
   const size_t rb = (size_t)row * D;
-  f32x4 v[NV], gv[NV];
+  fv v[NV], gv[NV];
   float ss = 0.f;
   // Every load first (input, gains, then the partial sums), so that one
   // memory latency covers them all; then the adds, in split order.
 #pragma unroll
   for (int i = 0; i < NV; ++i) {
-    const int c = (i * 256 + tid) * 4;
-    gv[i] = *(const f32x4 *)(gain + c);
-    if constexpr (std::is_same<TI, float>::value) {
-      v[i] = *(const f32x4 *)(in + rb + c);
-    } else {
-      const bf16x4 b = *(const bf16x4 *)(in + rb + c);
-      v[i] = (f32x4){(float)b[0], (float)b[1], (float)b[2], (float)b[3]};
-    }
+    const int c = (i * 256 + tid) * VW;
+    gv[i] = *(const fv *)(gain + c);
+    const tivu x = *(const tivu *)(in + rb + c);
+#pragma unroll
+    for (int e = 0; e < VW; ++e) v[i][e] = to_f32(x[e]);
   }
-  f32x4 q[kMaxParts][NV];
+  fv q[kMaxParts][NV];
 #pragma unroll
   for (int k = 0; k < kMaxParts; ++k)
     if (k < pt.np)
 #pragma unroll
-      for (int i = 0; i < NV; ++i) q[k][i] = *(const f32x4 *)(pt.p + (size_t)k * pt.stride + rb + (i * 256 + tid) * 4);
+      for (int i = 0; i < NV; ++i) q[k][i] = *(const fv *)(pt.p + (size_t)k * pt.stride + rb + (i * 256 + tid) * VW);
 #pragma unroll
   for (int k = 0; k < kMaxParts; ++k)
     if (k < pt.np)
 #pragma unroll
       for (int i = 0; i < NV; ++i)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) v[i][e] += q[k][i][e];
+        for (int e = 0; e < VW; ++e) v[i][e] += q[k][i][e];
 #pragma unroll
   for (int i = 0; i < NV; ++i)
 #pragma unroll
-    for (int e = 0; e < 4; ++e) ss += v[i][e] * v[i][e];
+    for (int e = 0; e < VW; ++e) ss += v[i][e] * v[i][e];
 #pragma unroll
   for (int m = 32; m >= 1; m >>= 1) ss = warp_sum_xor(ss, m);
   if ((tid & 63) == 0) red[tid >> 6] = ss;
@@ -119,62 +184,87 @@ __global__ __launch_bounds__(256) void k_rmsnorm_vec(const TI *in, float *copy_t
   const float rs = rsqrtf((red[0] + red[1] + red[2] + red[3]) / (float)D + eps);
 #pragma unroll
   for (int i = 0; i < NV; ++i) {
-    const int c = (i * 256 + tid) * 4;
-    if (copy_to) *(f32x4 *)(copy_to + rb + c) = v[i];
-    f32x4 y;
+    const int c = (i * 256 + tid) * VW;
+    if (copy_to) *(fvu *)(copy_to + rb + c) = v[i];
+    typedef typename std::conditional<OUT_FMT == FMT_F32, float,
+                                      typename std::conditional<OUT_FMT == FMT_BF16, bf16, f16>::type>::type TO;
+    typedef typename VecOf<TO, VW>::type tovu __attribute__((aligned(sizeof(TO))));
+    tovu y;
 #pragma unroll
-    for (int e = 0; e < 4; ++e) y[e] = v[i][e] * rs * gv[i][e];
-    if constexpr (OUT_FMT == FMT_F32) {
-      *(f32x4 *)((float *)out + rb + c) = y;
-    } else if constexpr (OUT_FMT == FMT_BF16) {
-      bf16x4 h;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) h[e] = (bf16)y[e];
-      *(bf16x4 *)((bf16 *)out + rb + c) = h;
-    } else {
-      f16x4 h;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) h[e] = (f16)y[e];
-      *(f16x4 *)((f16 *)out + rb + c) = h;
-    }
+    for (int e = 0; e < VW; ++e) y[e] = (TO)(v[i][e] * rs * gv[i][e]);
+    *(tovu *)((TO *)out + rb + c) = y;
   }
 }
 
-template <typename TI, int NV>
-static void rmsnorm_vec(int out_fmt, dim3 grid, const TI *in, float *copy_to, const Parts &pt,
-                        const float *g, void *out, int D, float eps, hipStream_t s) {
+template <typename TI, int VW, int NV>
+static hipError_t rmsnorm_vec(int out_fmt, int rows, const TI *in, float *copy_to, const Parts &pt, const float *g,
+                              void *out, int D, float eps, const RopeJob *rope, hipStream_t s) {
+  if (rope) {
+    // (the table opens a forward, whose first norm feeds the projections)
+    const dim3 grid(rows + rope->blocks);
+    if (out_fmt == FMT_F32)
+      hipLaunchKernelGGL((k_rmsnorm_vec<TI, FMT_F32, VW, NV, true>), grid, dim3(256), 0, s, in, copy_to, pt, g, out, D,
+                         eps, *rope);
+    else if (out_fmt == FMT_F16)
+      hipLaunchKernelGGL((k_rmsnorm_vec<TI, FMT_F16, VW, NV, true>), grid, dim3(256), 0, s, in, copy_to, pt, g, out, D,
+                         eps, *rope);
+    else
+      return hipErrorInvalidValue;
+    return hipGetLastError();
+  }
+  const dim3 grid(rows);
   if (out_fmt == FMT_F32)
-    hipLaunchKernelGGL((k_rmsnorm_vec<TI, FMT_F32, NV>), grid, dim3(256), 0, s, in, copy_to, pt, g, out, D, eps);
+    hipLaunchKernelGGL((k_rmsnorm_vec<TI, FMT_F32, VW, NV, false>), grid, dim3(256), 0, s, in, copy_to, pt, g, out, D,
+                       eps, NoRope{});
   else if (out_fmt == FMT_BF16)
-    hipLaunchKernelGGL((k_rmsnorm_vec<TI, FMT_BF16, NV>), grid, dim3(256), 0, s, in, copy_to, pt, g, out, D, eps);
+    hipLaunchKernelGGL((k_rmsnorm_vec<TI, FMT_BF16, VW, NV, false>), grid, dim3(256), 0, s, in, copy_to, pt, g, out, D,
+                       eps, NoRope{});
   else
-    hipLaunchKernelGGL((k_rmsnorm_vec<TI, FMT_F16, NV>), grid, dim3(256), 0, s, in, copy_to, pt, g, out, D, eps);
+    hipLaunchKernelGGL((k_rmsnorm_vec<TI, FMT_F16, VW, NV, false>), grid, dim3(256), 0, s, in, copy_to, pt, g, out, D,
+                       eps, NoRope{});
+  return hipGetLastError();
 }
 
 template <typename TI>
-static void rmsnorm_dispatch(int out_fmt, dim3 grid, const TI *in, float *copy_to, const Parts &pt,
-                             const float *g, void *out, int D, float eps, hipStream_t s) {
-  switch (D % 1024 == 0 ? D / 1024 : 0) {
-    case 1: rmsnorm_vec<TI, 1>(out_fmt, grid, in, copy_to, pt, g, out, D, eps, s); break;
-    case 2: rmsnorm_vec<TI, 2>(out_fmt, grid, in, copy_to, pt, g, out, D, eps, s); break;
-    case 3: rmsnorm_vec<TI, 3>(out_fmt, grid, in, copy_to, pt, g, out, D, eps, s); break;
-    case 4: rmsnorm_vec<TI, 4>(out_fmt, grid, in, copy_to, pt, g, out, D, eps, s); break;
-    default: rmsnorm_out<TI>(out_fmt, grid, in, copy_to, pt, g, out, D, eps, s); break;
+static hipError_t rmsnorm_dispatch(int out_fmt, int rows, const TI *in, float *copy_to, const Parts &pt,
+                                   const float *g, void *out, int D, float eps, const RopeJob *rope, hipStream_t s) {
+  switch (D % 256 == 0 ? D / 256 : 0) {
+#define MTE_NORM(n, vw, nv) case n: return rmsnorm_vec<TI, vw, nv>(out_fmt, rows, in, copy_to, pt, g, out, D, eps, rope, s);
+    MTE_NORM(4, 4, 1) MTE_NORM(8, 4, 2) MTE_NORM(12, 4, 3) MTE_NORM(16, 4, 4)
+    MTE_NORM(2, 2, 1) MTE_NORM(6, 2, 3) MTE_NORM(10, 2, 5)
+    MTE_NORM(1, 1, 1) MTE_NORM(3, 1, 3) MTE_NORM(5, 1, 5)
+#undef MTE_NORM
   }
+  if (rope) {
+    hipLaunchKernelGGL(k_rope_table, dim3(rope->blocks), dim3(256), 0, s, *rope);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  rmsnorm_out<TI>(out_fmt, dim3(rows), in, copy_to, pt, g, out, D, eps, s);
+  return hipGetLastError();
+}
+
+static hipError_t rmsnorm(int in_fmt, int out_fmt, const void *in, float *copy_to, const float *parts, int nparts,
+                          const float *g, void *out, int rows, int D, float eps, const RopeJob *rope, hipStream_t s) {
+  if (rows <= 0) return hipSuccess;
+  if (parts && nparts > kMaxParts) return hipErrorInvalidValue;
+  const Parts pt{parts, parts ? nparts : 0, (size_t)rows * D};
+  if (in_fmt == FMT_BF16)
+    return rmsnorm_dispatch<bf16>(out_fmt, rows, (const bf16 *)in, copy_to, pt, g, out, D, eps, rope, s);
+  return rmsnorm_dispatch<float>(out_fmt, rows, (const float *)in, copy_to, pt, g, out, D, eps, rope, s);
 }
 
 hipError_t launch_rmsnorm(int in_fmt, int out_fmt, const void *in, float *copy_to, const float *parts,
                           int nparts, const float *g, void *out, int rows, int D, float eps,
                           hipStream_t s) {
-  if (rows <= 0) return hipSuccess;
-  if (parts && nparts > kMaxParts) return hipErrorInvalidValue;
-  dim3 grid(rows);
-  const Parts pt{parts, parts ? nparts : 0, (size_t)rows * D};
-  if (in_fmt == FMT_BF16)
-    rmsnorm_dispatch<bf16>(out_fmt, grid, (const bf16 *)in, copy_to, pt, g, out, D, eps, s);
-  else
-    rmsnorm_dispatch<float>(out_fmt, grid, (const float *)in, copy_to, pt, g, out, D, eps, s);
-  return hipGetLastError();
+  return rmsnorm(in_fmt, out_fmt, in, copy_to, parts, nparts, g, out, rows, D, eps, nullptr, s);
+}
+
+hipError_t launch_first_norm(int in_fmt, int out_fmt, const void *in, float *copy_to, const float *g, void *out,
+                             int rows, int D, float eps, const int32_t *pos_thw, int half, const RopeParams &rp,
+                             float *rcos, float *rsin, hipStream_t s) {
+  const RopeJob r = rope_job(pos_thw, rows, half, rp, rcos, rsin);
+  return rmsnorm(in_fmt, out_fmt, in, copy_to, nullptr, 0, g, out, rows, D, eps, &r, s);
 }
 
 // h[r, c] += parts[0][r, c] + ... + parts[np-1][r, c], in that order.
@@ -389,33 +479,6 @@ hipError_t launch_swiglu_parts(int out_fmt, const float *parts, int nparts, int 
     hipLaunchKernelGGL(k_swiglu_parts<FMT_F32>, grid, dim3(256), 0, s, pt, F, out, out_scale, n);
   else
     hipLaunchKernelGGL(k_swiglu_parts<FMT_F16>, grid, dim3(256), 0, s, pt, F, out, out_scale, n);
-  return hipGetLastError();
-}
-
-// ---------------------------------------------------- rotary table
-// cos / sin of the rotation angle of every (token, pair): pair j of token
-// t turns by pos[axis(j)][t] * inv_freq[j]; the angle and its sincos are
-// evaluated in float64 and rounded to fp32. Built once per forward and
-// shared by the q and k heads of all layers.
-__global__ __launch_bounds__(256) void k_rope_table(const int32_t *__restrict__ pos, int T_tokens,
-                                                    int half, RopeParams rp, float *__restrict__ rcos,
-                                                    float *__restrict__ rsin) {
-  const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
-  if (i >= (size_t)T_tokens * half) return;
-  const int tok = (int)(i / half), j = (int)(i % half);
-  const double ang = (double)pos[(size_t)rp.axis[j] * T_tokens + tok] * rp.inv_freq[j];
-  double sv, cv;
-  sincos(ang, &sv, &cv);
-  rcos[i] = (float)cv;
-  rsin[i] = (float)sv;
-}
-
-hipError_t launch_rope_table(const int32_t *pos_thw, int T, int half, const RopeParams &rp, float *rcos,
-                             float *rsin, hipStream_t s) {
-  const size_t n = (size_t)T * half;
-  if (n == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_rope_table, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, pos_thw, T, half,
-                     rp, rcos, rsin);
   return hipGetLastError();
 }
 
