@@ -342,8 +342,9 @@ int mte_encoder_create(const mte_config *cfg, const mte_weights *w, hipStream_t 
     if (he != hipSuccess) return fail(MTE_E_HIP);
   }
 
-  // Repack: fused [Wq; Wk; Wv], gate/up interleaved in blocks of 16 rows,
-  // converted to the operand type with the weight pre-scales; fp32 norm
+  // Repack: fused [Wq; Wk; Wv], gate/up interleaved in blocks of 16 rows, each
+  // in the GEMMs' blocked layout (parts of a fused matrix start at multiples of
+  // 16 rows), converted to the operand type with the weight pre-scales; fp32 norm
   // gains with the activation pre-scales folded in.
   const double sqrtD = std::sqrt((double)D);
   for (int l = 0; l < c.n_layers && he == hipSuccess; ++l) {
@@ -410,24 +411,24 @@ int mte_encoder_create(const mte_config *cfg, const mte_weights *w, hipStream_t 
       o.cs_d = cs + nqkv + D + 2 * F;
       uint8_t *q = (uint8_t *)o.w_qkv;
       float *qs = (float *)o.cs_qkv;
-      he = launch_quantize_e4m3_rows(sf, L.w_q, (int)(Hq * d), (int)D, q, qs, 0, 0, stream);
+      he = launch_quantize_e4m3_rows(sf, L.w_q, (int)(Hq * d), (int)D, q, qs, 0, 0, 1, stream);
       if (he == hipSuccess)
-        he = launch_quantize_e4m3_rows(sf, L.w_k, (int)(Hkv * d), (int)D, q + Hq * d * D, qs + Hq * d, 0, 0,
+        he = launch_quantize_e4m3_rows(sf, L.w_k, (int)(Hkv * d), (int)D, q + Hq * d * D, qs + Hq * d, 0, 0, 1,
                                        stream);
       if (he == hipSuccess)
         he = launch_quantize_e4m3_rows(sf, L.w_v, (int)(Hkv * d), (int)D, q + (Hq + Hkv) * d * D,
-                                       qs + (Hq + Hkv) * d, 0, 0, stream);
+                                       qs + (Hq + Hkv) * d, 0, 0, 1, stream);
       if (he == hipSuccess)
         he = launch_quantize_e4m3_rows(sf, L.w_o, (int)D, (int)(Hq * d), (uint8_t *)o.w_o, (float *)o.cs_o, 0,
-                                       0, stream);
+                                       0, 1, stream);
       if (he == hipSuccess)
         he = launch_quantize_e4m3_rows(sf, L.w_gate, (int)F, (int)D, (uint8_t *)o.w_gu, (float *)o.cs_gu, 1,
-                                       0, stream);
+                                       0, 1, stream);
       if (he == hipSuccess)
-        he = launch_quantize_e4m3_rows(sf, L.w_up, (int)F, (int)D, (uint8_t *)o.w_gu, (float *)o.cs_gu, 1, 1,
+        he = launch_quantize_e4m3_rows(sf, L.w_up, (int)F, (int)D, (uint8_t *)o.w_gu, (float *)o.cs_gu, 1, 1, 1,
                                        stream);
       if (he == hipSuccess)
-        he = launch_quantize_e4m3_rows(sf, L.w_down, (int)D, (int)F, (uint8_t *)o.w_d, (float *)o.cs_d, 0, 0,
+        he = launch_quantize_e4m3_rows(sf, L.w_down, (int)D, (int)F, (uint8_t *)o.w_d, (float *)o.cs_d, 0, 0, 1,
                                        stream);
     } else {
       he = launch_convert_rows(sf, L.w_q, df, o.w_qkv, (int)(Hq * d), (int)D, sq, 0, 0, stream);
@@ -852,7 +853,7 @@ int mte_quantize_e4m3_rows(const void *src, int32_t src_dtype, int32_t rows, int
                            float *scales, hipStream_t stream) {
   if (!src || !codes || !scales || rows <= 0 || cols <= 0) return MTE_E_INVALID;
   if (src_dtype != MTE_F32 && src_dtype != MTE_BF16) return MTE_E_INVALID;
-  return launch_quantize_e4m3_rows(in_fmt(src_dtype), src, rows, cols, codes, scales, 0, 0, stream) ==
+  return launch_quantize_e4m3_rows(in_fmt(src_dtype), src, rows, cols, codes, scales, 0, 0, 0, stream) ==
                  hipSuccess
              ? MTE_OK
              : MTE_E_HIP;

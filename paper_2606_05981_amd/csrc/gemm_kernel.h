@@ -1,7 +1,8 @@
 // Projection GEMMs of the decoder layer on gfx950 matrix cores.
 //
 // C = A[M, K] * W[N, K]^T, A = activations (row-major, K contiguous),
-// W = weights in nn.Linear layout (row-major, K contiguous).
+// W = weights in blocks of 16 rows x one K stage (see packed_at where they are
+// written), so that a workgroup streams whole blocks.
 //
 // Precision modes:
 //  MODE_F32: A and W fp32, v_mfma_f32_16x16x4_f32.
@@ -318,7 +319,8 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) __attribute__((amdgpu_waves_per_
   const size_t rowb = (size_t)g.K * sizeof(T);    // row pitch in bytes (A; W unless W8)
   const size_t kb0 = (size_t)tz * g.k_chunk * sizeof(T);
   const size_t rowbw = W8 ? (size_t)g.K : rowb;
-  const size_t kb0w = W8 ? (size_t)tz * g.k_chunk : kb0;
+  constexpr int SBW = W8 ? ROWB / 2 : ROWB;       // bytes of a W row per stage
+  const size_t kb0w = (W8 ? (size_t)tz * g.k_chunk : kb0) * 16;
   const int nk = g.k_chunk / KS;
 
   // DMA sources: instruction c of this thread fills LDS slot q = (c*NW + wave)*64 + lane
@@ -340,7 +342,7 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) __attribute__((amdgpu_waves_per_
 #pragma unroll
   for (int c = 0; c < (BSTRIDE ? 1 : BR); ++c) {
     const int q = min(c * NW + wave, BG - 1) * 64 + lane, r = q / CHW, ch = swz<CHW>(r, q % CHW);
-    pb[c] = (uint32_t)((size_t)(n0 + r) * rowbw + ch * 16);
+    pb[c] = (uint32_t)((size_t)((n0 + r) & ~15) * rowbw + (r & 15) * SBW + ch * 16);
   }
   const uint32_t lds0 = (uint32_t)(uintptr_t)lds;
   const int uwave = __builtin_amdgcn_readfirstlane(wave);   // wave-uniform in an SGPR
@@ -352,7 +354,7 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) __attribute__((amdgpu_waves_per_
       dma16(g.A + kb0 + ko, pa[x], st + (uint32_t)(min(x * NW + uwave, AG - 1) * 64) * 16u);
     } else {
       const int c = x - AR;
-      const char *wb = g.W + kb0w + (W8 ? ko / 2 : ko);
+      const char *wb = g.W + kb0w + (size_t)ks * (16 * SBW);
       if constexpr (BSTRIDE) dma16(wb + c * bstep, pb[0], st + (uint32_t)(ACH + min(c * NW + uwave, BG - 1) * 64) * 16u);
       else dma16(wb, pb[c], st + (uint32_t)(ACH + min(c * NW + uwave, BG - 1) * 64) * 16u);
     }

@@ -60,7 +60,9 @@ struct QkvEpi {
 };
 
 // C = A[M, K] * W[N, K]^T, A and W of the mode's operand type (float or
-// fp16). The product is multiplied by `scale` (the inverse of the operands'
+// fp16), A row-major, W in blocks of 16 rows x 128 bytes of K (64 for e4m3
+// codes), each contiguous, those of the same 16 rows one after the other along
+// K. The product is multiplied by `scale` (the inverse of the operands'
 // power-of-two pre-scales; exact) before the epilogue; EPI_SWIGLU multiplies
 // its fp16 output by `out_scale` (a power of two keeping it in fp16 range).
 // ldc: C's row pitch in elements.
@@ -190,7 +192,8 @@ hipError_t launch_matrix_stats(int src_fmt, const void *src, int rows, int cols,
                                hipStream_t s);
 
 // Converts rows [0, rows) of src (format src_fmt, cols columns) into
-// dst_fmt (bf16 -> FMT_F16, f32 -> FMT_F32 or FMT_BF16) times `scale` (a power of two), writing
+// dst_fmt (bf16 -> FMT_F16, f32 -> FMT_F32) times `scale` (a power of two), in the
+// weight layout of launch_gemm (cols a multiple of its 128 bytes of K), writing
 // source row r to destination row map(r): map(r) = r, or with `interleave`
 // the gate/up packing (src = gate or up of F = rows rows: gate row f goes to
 // 32*(f/16) + f%16, up row f to 32*(f/16) + 16 + f%16, `up` selecting which).
@@ -222,8 +225,9 @@ hipError_t launch_scatter_rows(const float *src, int dst_fmt, void *dst, int row
 // all-zero row), and code(src[r, c] / 2^e_r) per element, rounded to
 // nearest, ties to even (the division is exact), zero as +0. Source row r
 // goes to destination row map(r) of codes (cols bytes per row) and scales,
-// map as in launch_convert_rows (interleave / up).
+// map as in launch_convert_rows (interleave / up). packed: codes in the weight
+// layout of launch_gemm (cols a multiple of 64), else row-major.
 hipError_t launch_quantize_e4m3_rows(int src_fmt, const void *src, int rows, int cols, uint8_t *codes,
-                                     float *scales, int interleave, int up, hipStream_t s);
+                                     float *scales, int interleave, int up, int packed, hipStream_t s);
 
 }  // namespace mte
