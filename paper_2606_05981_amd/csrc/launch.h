@@ -110,9 +110,10 @@ struct RopeParams {
   uint8_t axis[64];          // position axis (0 t, 1 h, 2 w) of pair j
 };
 
-// The two kernels that open a forward, in one launch: launch_rmsnorm without
-// partial sums (out_fmt FMT_F32 or FMT_F16), and launch_rope_table of the
-// `rows` tokens.
+// The opening of a forward in one launch: launch_rmsnorm without partial sums
+// (out_fmt FMT_F32 or FMT_F16), and the rotary table of the `rows` tokens, rcos /
+// rsin [rows, half] = cos / sin of pos_thw[axis(j)][t] * inv_freq[j] (float64 angle
+// and sincos, rounded).
 hipError_t launch_first_norm(int in_fmt, int out_fmt, const void *in, float *copy_to, const float *g, void *out,
                              int rows, int D, float eps, const int32_t *pos_thw, int half, const RopeParams &rp,
                              float *rcos, float *rsin, hipStream_t s);
@@ -127,11 +128,6 @@ hipError_t launch_resid_add(float *h, const float *parts, int nparts, int rows, 
 // FMT_F16 [rows, F].
 hipError_t launch_swiglu_parts(int out_fmt, const float *parts, int nparts, int rows, int F, void *out,
                                float out_scale, hipStream_t s);
-
-// Rotary table of T tokens: rcos / rsin [T, half] = cos / sin of
-// pos_thw[axis(j)][t] * inv_freq[j] (float64 angle and sincos, rounded).
-hipError_t launch_rope_table(const int32_t *pos_thw, int T, int half, const RopeParams &rp, float *rcos,
-                             float *rsin, hipStream_t s);
 
 // QKV projection finished from nparts partial sums [T, (Hq+2Hkv)*d]
 // (T*(Hq+2Hkv)*d elements apart, added in order) into qkv, with the q and k
@@ -200,15 +196,17 @@ hipError_t launch_matrix_stats(int src_fmt, const void *src, int rows, int cols,
 hipError_t launch_convert_rows(int src_fmt, const void *src, int dst_fmt, void *dst, int rows, int cols,
                                float scale, int interleave, int up, hipStream_t s);
 
-// Vision tower. Patches of n images [n, C, H, W] (in_fmt FMT_F32 / FMT_BF16)
+// Vision tower, its opening in one launch. Patches of n images [n, C, H, W]
+// (in_fmt FMT_F32 / FMT_BF16)
 // -> out [n * (H/patch) * (W/patch), C*patch*patch] (out_fmt FMT_F32 / FMT_F16),
 // patches of an image in merge-group order (groups of merge x merge patches
 // row-major over the image, row-major inside a group), each patch's vector in
-// (channel, row, column) order. H and W multiples of patch * merge.
-hipError_t launch_patchify(int in_fmt, const void *pixels, int n, int C, int H, int W, int patch, int merge,
-                           int out_fmt, void *out, hipStream_t s);
-// pos [3, n * patches per image]: t = 0, h = patch row, w = patch column (same order).
-hipError_t launch_patch_positions(int32_t *pos, int n, int H, int W, int patch, int merge, hipStream_t s);
+// (channel, row, column) order. H and W multiples of patch * merge. And the
+// rotary table rcos / rsin [patches, half] of (t, h, w) = (0, patch row, patch
+// column), as in launch_first_norm.
+hipError_t launch_vision_open(int in_fmt, const void *pixels, int n, int C, int H, int W, int patch, int merge,
+                              int out_fmt, void *out, int half, const RopeParams &rp, float *rcos, float *rsin,
+                              hipStream_t s);
 // y[r] = (x[r] - mean) / sqrt(var + eps) * g + b per row of x (float [rows, D],
 // D <= 4096); y in out_fmt (FMT_F32 / FMT_F16).
 hipError_t launch_layernorm(const float *x, const float *g, const float *b, int out_fmt, void *y, int rows, int D,

@@ -38,14 +38,6 @@ static RopeJob rope_job(const int32_t *pos_thw, int T, int half, const RopeParam
 
 __global__ __launch_bounds__(256) void k_rope_table(RopeJob r) { rope_block(r, blockIdx.x); }
 
-hipError_t launch_rope_table(const int32_t *pos_thw, int T, int half, const RopeParams &rp, float *rcos,
-                             float *rsin, hipStream_t s) {
-  if ((size_t)T * half == 0) return hipSuccess;
-  const RopeJob r = rope_job(pos_thw, T, half, rp, rcos, rsin);
-  hipLaunchKernelGGL(k_rope_table, dim3(r.blocks), dim3(256), 0, s, r);
-  return hipGetLastError();
-}
-
 // ------------------------------------------------------------- RMSNorm
 // out = x / sqrt(mean(x^2) + eps) * g, one 256-thread block per row, where
 // x = in + the np partial sums parts[0..np) (pitch pstride elements), added

@@ -61,7 +61,6 @@ struct mte_vision {
   void *act = nullptr;      // [T, F]
   void *mact = nullptr;     // [T/mm, mm D]
   float *mout = nullptr;    // [T/mm, out_hidden] (bf16 output only)
-  int32_t *pos = nullptr;   // [3, T]
   float *rcos = nullptr, *rsin = nullptr;
   RopeParams rope;
 };
@@ -102,7 +101,7 @@ void mte_vision_destroy(mte_vision *e) {
   hipSetDevice(e->device);
   hipDeviceSynchronize();
   for (void *p : {e->wbuf, (void *)e->fbuf, e->patches, (void *)e->h, e->xn, (void *)e->qkv, e->attn, e->act, e->mact,
-                  (void *)e->mout, (void *)e->pos, (void *)e->rcos, (void *)e->rsin})
+                  (void *)e->mout, (void *)e->rcos, (void *)e->rsin})
     hipFree(p);
   hipSetDevice(cur);
   delete e;
@@ -147,7 +146,6 @@ int mte_vision_create(const mte_vision_config *cfg, const mte_vision_weights *w,
       hipMalloc(&e->xn, T * D * es) != hipSuccess || hipMalloc((void **)&e->qkv, std::max(T * 3 * D * 4, ((T * 2 * D * 2 + 255) & ~(size_t)255) + (T + 31) / 32 * 32 * D * 2)) != hipSuccess ||
       hipMalloc(&e->attn, T * D * es) != hipSuccess || hipMalloc(&e->act, T * F * es) != hipSuccess ||
       hipMalloc(&e->mact, T * D * es) != hipSuccess || hipMalloc((void **)&e->mout, (T / mm + 1) * DO * 4) != hipSuccess ||
-      hipMalloc((void **)&e->pos, 3 * T * 4) != hipSuccess ||
       hipMalloc((void **)&e->rcos, T * (c.head_dim / 2) * 4) != hipSuccess ||
       hipMalloc((void **)&e->rsin, T * (c.head_dim / 2) * 4) != hipSuccess)
     return fail(MTE_E_OOM);
@@ -328,9 +326,8 @@ int mte_vision_encode_strided(mte_vision *e, const void *pixels, int32_t n, int3
   int sp = 0;
   hipError_t err = hipSuccess;
 #define MTE_TRY(x) do { err = (x); if (err != hipSuccess) goto done; } while (0)
-  MTE_TRY(launch_patchify(v_in_fmt(c.dtype), pixels, n, c.in_channels, H, W, c.patch, c.merge, af, e->patches, s));
-  MTE_TRY(launch_patch_positions(e->pos, n, H, W, c.patch, c.merge, s));
-  MTE_TRY(launch_rope_table(e->pos, T, hd / 2, e->rope, e->rcos, e->rsin, s));
+  MTE_TRY(launch_vision_open(v_in_fmt(c.dtype), pixels, n, c.in_channels, H, W, c.patch, c.merge, af, e->patches,
+                             hd / 2, e->rope, e->rcos, e->rsin, s));
   MTE_TRY(launch_gemm(mode, EPI_STORE, e->patches, e->w_patch, e->h, T, D, KP, D, e->s_patch, 1.f, nullptr, 0, &sp,
                       nullptr, s, nullptr, e->b_patch));
   for (int l = 0; l < c.depth; ++l) {

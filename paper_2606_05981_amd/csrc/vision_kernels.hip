@@ -1,5 +1,5 @@
 // Row-wise kernels of the vision tower: patch extraction in merge-group
-// order, LayerNorm, and the (row, column) positions of the patches.
+// order with the rotary table of the patches' places, and LayerNorm.
 #include "common.h"
 #include "launch.h"
 
@@ -23,55 +23,73 @@ __device__ __forceinline__ void patch_rc(const PatchGeom &g, int p, int &ph, int
   pw = g.merge * (grp % g.gw) + in % g.merge;
 }
 
-template <typename TI, typename TO>
-__global__ __launch_bounds__(256) void k_patchify(const TI *__restrict__ px, TO *__restrict__ out, PatchGeom g,
-                                                  size_t total) {
-  const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
+// The rotary entries of a patch depend on its place only: pair j turns by the
+// patch row (axis 1) or column (axis 2) times inv_freq[j], angle and sincos in
+// float64, rounded.
+__device__ __forceinline__ void patch_rope(const PatchGeom &g, const RopeParams &rp, int T, int half, size_t i,
+                                           float *rcos, float *rsin) {
+  if (i >= (size_t)T * half) return;
+  const int tok = (int)(i / half), j = (int)(i % half);
+  int ph, pw;
+  patch_rc(g, tok % g.per_image, ph, pw);
+  const double ang = (double)(rp.axis[j] == 1 ? ph : rp.axis[j] == 2 ? pw : 0) * rp.inv_freq[j];
+  double sv, cv;
+  sincos(ang, &sv, &cv);
+  rcos[i] = (float)cv;
+  rsin[i] = (float)sv;
+}
+
+// One launch opens the tower: the first rope_blocks blocks build the rotary
+// table (256 entries each), the others extract patches, V consecutive values
+// of a patch row per thread. V = 8 (16-byte accesses of bf16 pixels) where a
+// patch row is a multiple of 8 pixels, else 1. Bound by memory; one value per
+// thread, with its divisions, took 20 us for 16 images of 256x256 (6.3 MB in, 6.3
+// MB out), and the positions and the table 5 us each in launches of their own.
+template <typename TI, typename TO, int V>
+__global__ __launch_bounds__(256) void k_vision_open(const TI *__restrict__ px, TO *__restrict__ out, PatchGeom g,
+                                                     size_t total, RopeParams rp, int T, int half, int rope_blocks,
+                                                     float *__restrict__ rcos, float *__restrict__ rsin) {
+  if ((int)blockIdx.x < rope_blocks) {
+    patch_rope(g, rp, T, half, (size_t)blockIdx.x * 256 + threadIdx.x, rcos, rsin);
+    return;
+  }
+  typedef TI vi __attribute__((ext_vector_type(V), aligned(sizeof(TI))));   // pixels: a caller's buffer
+  typedef TO vo __attribute__((ext_vector_type(V)));
+  const size_t i = ((size_t)(blockIdx.x - rope_blocks) * 256 + threadIdx.x) * V;
   if (i >= total) return;
   const int K = g.C * g.patch * g.patch;
-  const size_t row = i / K;
-  const int k = (int)(i % K);
-  const int n = (int)(row / g.per_image), p = (int)(row % g.per_image);
+  const int row = (int)(i / K), k = (int)(i % K);
+  const int n = row / g.per_image, p = row % g.per_image;
   int ph, pw;
   patch_rc(g, p, ph, pw);
-  const int c = k / (g.patch * g.patch), ky = (k / g.patch) % g.patch, kx = k % g.patch;
+  const int pp = g.patch * g.patch;
+  const int c = k / pp, ky = (k % pp) / g.patch, kx = k % g.patch;
   const size_t src = (((size_t)n * g.C + c) * g.H + (size_t)ph * g.patch + ky) * g.W + (size_t)pw * g.patch + kx;
-  out[i] = from_f32<TO>(to_f32(px[src]));
+  const vi x = *(const vi *)(px + src);
+  vo y;
+#pragma unroll
+  for (int e = 0; e < V; ++e) y[e] = from_f32<TO>(to_f32(x[e]));
+  *(vo *)(out + i) = y;
 }
 
-hipError_t launch_patchify(int in_fmt, const void *pixels, int n, int C, int H, int W, int patch, int merge,
-                           int out_fmt, void *out, hipStream_t s) {
+hipError_t launch_vision_open(int in_fmt, const void *pixels, int n, int C, int H, int W, int patch, int merge,
+                              int out_fmt, void *out, int half, const RopeParams &rp, float *rcos, float *rsin,
+                              hipStream_t s) {
   if (n <= 0) return hipSuccess;
   if (H % (patch * merge) || W % (patch * merge)) return hipErrorInvalidValue;
-  PatchGeom g{C, H, W, patch, merge, W / (patch * merge), (H / patch) * (W / patch)};
-  const size_t total = (size_t)n * g.per_image * C * patch * patch;
-  const dim3 grid((unsigned)((total + 255) / 256));
-  if (in_fmt == FMT_BF16 && out_fmt == FMT_F16)
-    hipLaunchKernelGGL((k_patchify<bf16, f16>), grid, dim3(256), 0, s, (const bf16 *)pixels, (f16 *)out, g, total);
-  else if (in_fmt == FMT_F32 && out_fmt == FMT_F32)
-    hipLaunchKernelGGL((k_patchify<float, float>), grid, dim3(256), 0, s, (const float *)pixels, (float *)out, g,
-                       total);
-  else
-    return hipErrorInvalidValue;
-  return hipGetLastError();
-}
-
-// pos [3, T]: t = 0, h = patch row, w = patch column of every patch.
-__global__ __launch_bounds__(256) void k_patch_positions(int32_t *__restrict__ pos, int T, PatchGeom g) {
-  const int i = blockIdx.x * 256 + threadIdx.x;
-  if (i >= T) return;
-  int ph, pw;
-  patch_rc(g, i % g.per_image, ph, pw);
-  pos[i] = 0;
-  pos[T + i] = ph;
-  pos[2 * T + i] = pw;
-}
-
-hipError_t launch_patch_positions(int32_t *pos, int n, int H, int W, int patch, int merge, hipStream_t s) {
-  if (n <= 0) return hipSuccess;
-  PatchGeom g{0, H, W, patch, merge, W / (patch * merge), (H / patch) * (W / patch)};
+  const PatchGeom g{C, H, W, patch, merge, W / (patch * merge), (H / patch) * (W / patch)};
   const int T = n * g.per_image;
-  hipLaunchKernelGGL(k_patch_positions, dim3((T + 255) / 256), dim3(256), 0, s, pos, T, g);
+  const size_t total = (size_t)T * C * patch * patch;
+  const int v = patch % 8 == 0 ? 8 : 1;          // then every vector lies in one patch row
+  const int rope_blocks = (int)(((size_t)T * half + 255) / 256);
+  const dim3 grid((unsigned)(rope_blocks + (total / v + 255) / 256));
+#define MTE_OPEN(TI, TO, V)                                                                                     \
+  hipLaunchKernelGGL((k_vision_open<TI, TO, V>), grid, dim3(256), 0, s, (const TI *)pixels, (TO *)out, g, total, \
+                     rp, T, half, rope_blocks, rcos, rsin)
+  if (in_fmt == FMT_BF16 && out_fmt == FMT_F16) { if (v == 8) MTE_OPEN(bf16, f16, 8); else MTE_OPEN(bf16, f16, 1); }
+  else if (in_fmt == FMT_F32 && out_fmt == FMT_F32) { if (v == 8) MTE_OPEN(float, float, 8); else MTE_OPEN(float, float, 1); }
+  else return hipErrorInvalidValue;
+#undef MTE_OPEN
   return hipGetLastError();
 }
 
@@ -133,10 +151,19 @@ __global__ __launch_bounds__(256) void k_layernorm_wave(const float *__restrict_
   f32x4 v[NV];
   float s = 0.f;
 #pragma unroll
-  for (int k = 0; k < NV; ++k) {
-    v[k] = *(const f32x4 *)(xr + 4 * (lane + 64 * k));
-    s += (v[k][0] + v[k][1]) + (v[k][2] + v[k][3]);
+  for (int k = 0; k < NV; ++k) v[k] = *(const f32x4 *)(xr + 4 * (lane + 64 * k));
+  // up to 1024 values the gains and biases are loaded with the row (one memory
+  // latency for all); wider rows have no registers to spare for them
+  f32x4 gg[NV], bb[NV];
+  if constexpr (NV <= 4) {
+#pragma unroll
+    for (int k = 0; k < NV; ++k) {
+      gg[k] = *(const f32x4 *)(g + 4 * (lane + 64 * k));
+      bb[k] = *(const f32x4 *)(b + 4 * (lane + 64 * k));
+    }
   }
+#pragma unroll
+  for (int k = 0; k < NV; ++k) s += (v[k][0] + v[k][1]) + (v[k][2] + v[k][3]);
 #pragma unroll
   for (int m = 32; m >= 1; m >>= 1) s = warp_sum_xor(s, m);
   const float mean = s / (float)D;
@@ -155,9 +182,15 @@ __global__ __launch_bounds__(256) void k_layernorm_wave(const float *__restrict_
 #pragma unroll
   for (int k = 0; k < NV; ++k) {
     const int c = 4 * (lane + 64 * k);
-    const f32x4 gg = *(const f32x4 *)(g + c), bb = *(const f32x4 *)(b + c);
+    if constexpr (NV > 4) {
+      gg[k] = *(const f32x4 *)(g + c);
+      bb[k] = *(const f32x4 *)(b + c);
+    }
+    typedef TO vo __attribute__((ext_vector_type(4)));
+    vo y;
 #pragma unroll
-    for (int e = 0; e < 4; ++e) yr[c + e] = from_f32<TO>((v[k][e] - mean) * rs * gg[e] + bb[e]);
+    for (int e = 0; e < 4; ++e) y[e] = from_f32<TO>((v[k][e] - mean) * rs * gg[k][e] + bb[k][e]);
+    *(vo *)(yr + c) = y;
   }
 }
 
