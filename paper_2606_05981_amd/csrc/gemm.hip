@@ -7,7 +7,8 @@
 namespace mte {
 
 static const TileCfg kTiles[] = {
-#define MTE_TILE_INFO(id, bm, bn, wm, wn, p, occ, f32, su, tu) {bm, bn, wm, wn, p, occ, f32, su, tu},
+#define MTE_TILE_INFO(id, bm, bn, wm, wn, p, occ, f32, w8, su, tu, su8, tu8) \
+  {bm, bn, wm, wn, p, occ, f32, w8, su, tu, su8, tu8},
     MTE_TILE_TABLE(MTE_TILE_INFO)
 #undef MTE_TILE_INFO
 };
@@ -15,17 +16,24 @@ constexpr int kNumTiles = sizeof(kTiles) / sizeof(kTiles[0]);
 
 int gemm_num_tiles() { return kNumTiles; }
 
+// QKV on tile `id` with two waves of 64 columns per 128-wide head.
+static bool half_heads(int id, int epi, int col_align) {
+  const TileCfg &t = kTiles[id];
+  return epi == EPI_QKV && col_align == 128 && t.bn / t.wn == 64 && t.wn % 2 == 0;
+}
+
 // Whether tile `id` can run an (N, K, epilogue, splits) product: N a multiple of
 // its width, each K split a whole number of stages, fp32 operands only on the
 // tiles built for them. col_align: columns a wave must cover in whole units
-// (heads for the QKV epilogue, 32-column gate/up pairs for SwiGLU).
+// (heads for the QKV epilogue, which also takes two waves of 64 columns per
+// 128-wide head; 32-column gate/up pairs for SwiGLU).
 static bool tile_fits(int id, int N, int K, int esz, int epi, int splits, int col_align, bool w8) {
   const TileCfg &t = kTiles[id];
-  if (N % t.bn || (esz == 4 && !t.f32)) return false;
+  if (N % t.bn || (esz == 4 && !t.f32) || (w8 && !t.w8)) return false;
   if (t.p * (t.bm + (w8 ? t.bn / 2 : t.bn)) * kStageBytes * t.occ > 160 * 1024) return false;   // LDS ring
   const int ks = kStageBytes / esz;
   if (K % splits || (K / splits) % ks) return false;
-  if ((epi == EPI_QKV || epi == EPI_SWIGLU) && (t.bn / t.wn) % col_align) return false;
+  if ((epi == EPI_QKV || epi == EPI_SWIGLU) && (t.bn / t.wn) % col_align && !half_heads(id, epi, col_align)) return false;
   return true;
 }
 
@@ -67,7 +75,9 @@ static Plan plan_model(int M, int N, int K, int esz, int epi, int col_align, siz
       const TileCfg &t = kTiles[id];
       const int64_t wgs = (int64_t)(N / t.bn) * ((M + t.bm - 1) / t.bm) * sp;
       const double stages = (double)K / sp * esz / kStageBytes;
-      const double cost = 2.0 + tile_rounds(wgs, t.occ) * (stages * t.stage_us + t.tile_us) + add;
+      // (heads halved over two waves: 4% more, their exchange and second pass)
+      const double tile = w8 ? stages * t.stage_us_w8 + t.tile_us_w8 : stages * t.stage_us + t.tile_us;
+      const double cost = 2.0 + tile_rounds(wgs, t.occ) * tile * (half_heads(id, sp > 1 ? EPI_PARTIAL : epi, col_align) ? 1.04 : 1.0) + add;
       if (cost < cost_min) {
         cost_min = cost;
         best = Plan{id, sp};
