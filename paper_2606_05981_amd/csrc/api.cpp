@@ -507,10 +507,12 @@ struct PrefixCtx {
 };
 
 // Runs layers [l0, l1) on the fp32 residual stream `h` (T rows). The first
-// layer's attention norm is the caller's (launch_first_norm into wk.xn).
+// layer's attention norm is the caller's (launch_first_norm into wk.xn). h_in:
+// the stream's rows before the first layer where they are not in h yet (that
+// layer's output projection reads them there and writes h), or null.
 hipError_t run_layers(mte_encoder *e, const Work &wk, float *h, const int32_t *cu, int batch, int T, int l0,
                       int l1, int *pending, hipStream_t s,
-                      const PrefixCtx *pre = nullptr) {
+                      const PrefixCtx *pre = nullptr, const float *h_in = nullptr) {
   const mte_config &c = e->cfg;
   const int D = c.hidden, d = c.head_dim, Hq = c.n_q_heads, Hkv = c.n_kv_heads, F = c.ffn;
   const int nqkv = (Hq + 2 * Hkv) * d;
@@ -524,6 +526,7 @@ hipError_t run_layers(mte_encoder *e, const Work &wk, float *h, const int32_t *c
 #define MTE_TRY(x) do { err = (x); if (err != hipSuccess) return err; } while (0)
   for (int l = l0; l < l1; ++l) {
     const LayerW &W = e->layers[l];
+    const float *src = l == l0 && h_in ? h_in : h;   // the stream up to the output projection
     if (l > l0)
       MTE_TRY(launch_rmsnorm(FMT_F32, af, h, np ? h : nullptr, np ? ws : nullptr, np, W.attn_norm, wk.xn, T,
                              D, c.rms_eps, s));
@@ -571,9 +574,9 @@ hipError_t run_layers(mte_encoder *e, const Work &wk, float *h, const int32_t *c
     {
       Timer t(e, 2, s);
       MTE_TRY(launch_gemm(gm, EPI_RESID, wk.attn, W.w_o, h, T, D, Hq * d, D, W.s_o, 1.f, ws, wn, &np,
-                          nullptr, s, W.cs_o));
+                          nullptr, s, W.cs_o, nullptr, src));
     }
-    MTE_TRY(launch_rmsnorm(FMT_F32, af, h, np ? h : nullptr, np ? ws : nullptr, np, W.mlp_norm, wk.xn, T, D,
+    MTE_TRY(launch_rmsnorm(FMT_F32, af, np ? src : h, np ? h : nullptr, np ? ws : nullptr, np, W.mlp_norm, wk.xn, T, D,
                            c.rms_eps, s));
     {
       Timer t(e, 3, s);
@@ -727,13 +730,15 @@ int mte_encode_layers(mte_encoder *e, const float *h_in, const int32_t *pos_thw,
   if (layer_begin == layer_end) {
     if (h_out != h_in) err = hipMemcpyAsync(h_out, h_in, bytes, hipMemcpyDeviceToDevice, stream);
   } else {
-    // The first norm reads the residual stream anyway, so it also writes h_out
-    // (a copy of its own took 8 us of a 1536-row layer's 207, 30 us at 10240 rows).
-    err = launch_first_norm(FMT_F32, e->act_fmt, h_in, h_out != h_in ? h_out : nullptr,
+    // h_out is first written by the first layer's output projection, which reads
+    // h_in as its residual (also written by the first norm, h_out cost 16 us of a
+    // 6759-row layer's 700, 9 us of 1000 at 10240 rows, 2 us of 186 at 1536).
+    err = launch_first_norm(FMT_F32, e->act_fmt, h_in, nullptr,
                             e->layers[layer_begin].attn_norm, e->w.xn, T, e->cfg.hidden, e->cfg.rms_eps, pos_thw,
                             e->cfg.head_dim / 2, e->rope, e->w.rcos, e->w.rsin, stream);
     if (err == hipSuccess)
-      err = run_layers(e, e->w, h_out, cu.data(), batch, T, layer_begin, layer_end, &np, stream);
+      err = run_layers(e, e->w, h_out, cu.data(), batch, T, layer_begin, layer_end, &np, stream,
+                       nullptr, h_in);
   }
   if (err == hipSuccess && np) err = launch_resid_add(h_out, e->w.ws, np, T, e->cfg.hidden, stream);
   return err == hipSuccess ? MTE_OK : MTE_E_HIP;

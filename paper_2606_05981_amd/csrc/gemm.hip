@@ -122,7 +122,7 @@ hipError_t launch_mode_f8w(int epi, int tile, int splits, const GemmArgs &a, hip
 hipError_t launch_gemm_tile(int mode, int epi, int tile, int splits, const void *A, const void *W,
                             void *C, size_t c_plane, int M, int N, int K, int ldc, float scale,
                             float out_scale, const QkvEpi *qe, hipStream_t s, const float *col_scale,
-                            const float *bias) {
+                            const float *bias, const float *resid) {
   if (M <= 0) return hipSuccess;
   const bool w8 = mode == MODE_F8W;
   if (bias && (splits > 1 || epi == EPI_SWIGLU)) return hipErrorInvalidValue;
@@ -137,7 +137,8 @@ hipError_t launch_gemm_tile(int mode, int epi, int tile, int splits, const void 
     return hipErrorInvalidValue;
   const int gm = (M + kTiles[tile].bm - 1) / kTiles[tile].bm, gn = N / kTiles[tile].bn;
   GemmArgs a{(const char *)A, (const char *)W, C, c_plane, M, N, K, ldc, K / splits, scale, out_scale,
-             epi == EPI_QKV ? *qe : QkvEpi{}, w8 ? col_scale : nullptr, bias, gm, gn, gm < kGroupM ? gm : kGroupM};
+             epi == EPI_QKV ? *qe : QkvEpi{}, w8 ? col_scale : nullptr, bias,
+             resid ? resid : (const float *)C, gm, gn, gm < kGroupM ? gm : kGroupM};
   if (w8) return launch_mode_f8w(epi, tile, splits, a, s);
   return mode == MODE_F16 ? launch_mode<MODE_F16>(epi, tile, splits, a, s)
                           : launch_mode<MODE_F32>(epi, tile, splits, a, s);
@@ -146,7 +147,7 @@ hipError_t launch_gemm_tile(int mode, int epi, int tile, int splits, const void 
 hipError_t launch_gemm(int mode, int epi, const void *A, const void *W, void *C, int M, int N, int K,
                        int ldc, float scale, float out_scale, float *ws, size_t ws_elems,
                        int *splits_out, const QkvEpi *qe, hipStream_t s, const float *col_scale,
-                       const float *bias) {
+                       const float *bias, const float *resid) {
   *splits_out = 0;
   if (M <= 0) return hipSuccess;
   if (epi == EPI_QKV && !qe) return hipErrorInvalidValue;
@@ -159,7 +160,7 @@ hipError_t launch_gemm(int mode, int epi, const void *A, const void *W, void *C,
                             1.f, nullptr, s, col_scale);
   }
   return launch_gemm_tile(mode, epi, p.tile, 1, A, W, C, 0, M, N, K, ldc, scale, out_scale, qe, s, col_scale,
-                          bias);
+                          bias, resid);
 }
 
 }  // namespace mte

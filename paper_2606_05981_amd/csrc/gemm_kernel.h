@@ -79,6 +79,7 @@ struct GemmArgs {
   QkvEpi qe;          // EPI_QKV
   const float *cs;    // MODE_F8W: per-column (weight row) scales [N]
   const float *bias;  // [N] added to the product before the epilogue (unsplit launches), or null
+  const float *resid; // EPI_RESID: the residual stream that is read, C's shape and pitch (C itself, or rows that C takes over)
   // Order of the tiles: gm x gn tiles (M x N) per K split, in groups of gh M
   // tiles, a group column by column. Workgroup i of a launch runs on XCD i % 8;
   // XCD x takes the x-th contiguous eighth of that sequence, so the tiles it has
@@ -643,7 +644,7 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) __attribute__((amdgpu_waves_per_
     }
     return;
   }
-  // EPI_STORE / EPI_PARTIAL: C = scale * acc; EPI_RESID: C += scale * acc (one
+  // EPI_STORE / EPI_PARTIAL: C = scale * acc; EPI_RESID: C = resid + scale * acc (one
   // rounding: scale is a power of two), the old values of two 16-row blocks all
   // read before the first store so that their latencies overlap.
   float *C = (float *)g.C + (EPI == EPI_PARTIAL ? (size_t)tz * g.c_plane : 0) + cl;
@@ -654,7 +655,7 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) __attribute__((amdgpu_waves_per_
     if constexpr (EPI == EPI_RESID) {
 #pragma unroll
       for (int i = 0; i < IB; ++i) {
-        const float *p = C + (size_t)min(mw + (i0 + i) * 16 + lc, M - 1) * g.ldc;
+        const float *p = g.resid + cl + (size_t)min(mw + (i0 + i) * 16 + lc, M - 1) * g.ldc;
 #pragma unroll
         for (int j = 0; j < TN; ++j) old[i][j] = *(const f32x4u *)(p + j * 16);
       }

@@ -32,7 +32,7 @@ enum Epilogue {
   EPI_STORE = 0,   // C (float) [m, n] = scale * acc
   EPI_SWIGLU = 1,  // gate/up rows interleaved in blocks of 16: C[m, f] = out_scale *
                    // silu(gate) * up, written as float (MODE_F32) or fp16 (MODE_F16)
-  EPI_RESID = 2,   // C (float residual stream) [m, n] += scale * acc
+  EPI_RESID = 2,   // C (float residual stream) [m, n] = resid [m, n] + scale * acc (resid: C by default)
   EPI_PARTIAL = 3, // C (float) + split * c_plane [m, n] = scale * acc: one K split's partial sum
   EPI_QKV = 4,     // C (float) [m, n] = scale * acc, q and k heads RMS-normalised per head and rotated
   EPI_GELU = 5,    // C [m, n] = out_scale * gelu_tanh(scale * acc), float (MODE_F32) or fp16
@@ -79,10 +79,13 @@ struct QkvEpi {
 // epilogue; col_scale is ignored in the other modes.
 // bias: optional float [N] added to the product (after col_scale and `scale`, before the
 // epilogue); `scale` must then be a power of two, and the product is never K-split.
+// resid: EPI_RESID reads the residual stream here instead of from C (same shape and pitch, either
+// C or disjoint from it); null: C. With a K split the consumer has to.
 hipError_t launch_gemm(int mode, int epi, const void *A, const void *W, void *C, int M, int N, int K,
                        int ldc, float scale, float out_scale, float *ws, size_t ws_elems,
                        int *splits_out, const QkvEpi *qe, hipStream_t s,
-                       const float *col_scale = nullptr, const float *bias = nullptr);
+                       const float *col_scale = nullptr, const float *bias = nullptr,
+                       const float *resid = nullptr);
 
 // The same with an explicit tile configuration (index into the GEMM tile
 // table) and number of K splits (> 1 only with EPI_PARTIAL, partial sums
@@ -91,7 +94,8 @@ hipError_t launch_gemm(int mode, int epi, const void *A, const void *W, void *C,
 hipError_t launch_gemm_tile(int mode, int epi, int tile, int splits, const void *A, const void *W,
                             void *C, size_t c_plane, int M, int N, int K, int ldc, float scale,
                             float out_scale, const QkvEpi *qe, hipStream_t s,
-                            const float *col_scale = nullptr, const float *bias = nullptr);
+                            const float *col_scale = nullptr, const float *bias = nullptr,
+                       const float *resid = nullptr);
 int gemm_num_tiles();
 
 // Per-row RMSNorm: out[r, :] = x[r, :] / sqrt(mean(x[r,:]^2) + eps) * g with

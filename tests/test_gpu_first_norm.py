@@ -59,3 +59,29 @@ def test_residual_stream_buffers(dims):
         assert torch.equal(ref, inplace) and torch.equal(ref, dst)
         assert torch.equal(src, keep)
     enc.close()
+
+
+@pytest.mark.parametrize("dims,fmt,lens", [
+    (W.DIMS_TINY, 0, (64, 33)), (W.DIMS_FULL.with_(n_layers=2), 0, (320, 17, 300)),
+    (W.DIMS_FULL.with_(n_layers=2), 1, (320, 257)), (W.DIMS_FULL.with_(n_layers=2), 1, (1,)),
+], ids=["fp32_97", "bf16_637", "e4m3_577", "e4m3_1"])
+def test_residual_read_from_input(dims, fmt, lens):
+    """The first layer's output projection (whole or split over K) reads the input rows and writes
+    every element of h_out: the result equals the in-place one bit for bit, whatever h_out held."""
+    import torch
+    from paper_2606_05981_amd.encoder import build_positions
+    assert torch.cuda.is_available(), "no GPU"
+    T, D = sum(lens), dims.hidden
+    x = torch.from_numpy(np.random.default_rng(5).standard_normal((T, D), dtype=np.float32)).cuda()
+    keep = x.clone()
+    enc = make_encoder(dims, max_tokens=640, max_batch=4, max_seq=320, weight_format=fmt)
+    pos = build_positions([(n, 0, 0, 0, 0) for n in lens])
+    for l0, l1 in ((0, 1), (0, 2), (1, 2)):
+        print(T, "rows, layers", l0, l1, file=sys.stderr, flush=True)
+        inplace = x.clone()
+        enc.encode_layers(inplace, pos, list(lens), l0, l1, h_out=inplace)
+        out = torch.full_like(x, float("nan"))
+        enc.encode_layers(x, pos, list(lens), l0, l1, h_out=out)
+        torch.cuda.synchronize()
+        assert torch.equal(out, inplace) and torch.equal(x, keep)
+    enc.close()
