@@ -406,6 +406,20 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) __attribute__((amdgpu_waves_per_
   for (int i = 0; i < TM; ++i)
 #pragma unroll
     for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  // fp32 operands: the products of one stage (32 of K) are summed by themselves in
+  // `part` and then added to acc, so that a sum over K rounds K / 32 times at its
+  // full size, not K / 4 times. Unsplit products then keep the precision that 8 K
+  // splits give (two 256-wide layers against float64, mean over 8 inputs: 32 tokens
+  // 3.61e-7 and 2 x 128 tokens 4.15e-7; one chain 4.35e-7 and 7.11e-7; 8 splits
+  // 3.74e-7 and 4.35e-7).
+  constexpr bool STAGED = MODE == MODE_F32;
+  f32x4 part[STAGED ? TM : 1][STAGED ? TN : 1];
+  if constexpr (STAGED) {
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j) part[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
 
   constexpr int KK = CH / 4;                      // k-steps per stage
   static_assert(KK == 2, "fragment buffer parity");
@@ -460,8 +474,10 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) __attribute__((amdgpu_waves_per_
     if constexpr (W8) {
       if (RA ? o == 0 : y == 0) fb[0][j] = widen_e4m3(fw[RA ? cur : 0][j]);
     }
-    if constexpr (TRANS) mfma16(acc[i][j], fb[bw][j], fa[ba][i]);
-    else mfma16(acc[i][j], fa[ba][i], fb[bw][j]);
+    f32x4 *c = &acc[i][j];
+    if constexpr (STAGED) c = &part[i][j];
+    if constexpr (TRANS) mfma16(*c, fb[bw][j], fa[ba][i]);
+    else mfma16(*c, fa[ba][i], fb[bw][j]);
   };
   // The loads of stage kt+P are issued in NPART parts: part 0 right after the
   // barrier of stage kt, parts 1.. in the k-steps of stage kt+1 before its
@@ -541,6 +557,15 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) __attribute__((amdgpu_waves_per_
         const int d1 = (NPART > 1) ? min(PART, LOADS) : LOADS;
         kstep(cur, nx, 0, ksb, slb, 0, d1, true);
       }
+    }
+    if constexpr (STAGED) {
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+          acc[i][j] += part[i][j];
+          part[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
     }
   }
   wait_vm<0>();                          // no load may land after the workgroup ends

@@ -65,3 +65,23 @@ def test_fp32_rows(rows):
     x, pos, lens, got = run_layer(TINY, rows)
     ref = O.layer_forward(x, pos, lens, layer_w(TINY, 0), TINY)
     assert rel_err(got, ref) <= 1e-4
+
+
+@pytest.mark.parametrize("lens", [(32,), (128, 128), (320, 192)])
+def test_fp32_sums_in_stages(lens):
+    """The unsplit fp32 products sum K in stages of 32: the relative error of two layers and the
+    final norm against float64, averaged over four inputs, stays below 4.6e-7 (measured 3.6e-7,
+    4.2e-7 and 4.4e-7, single inputs within 0.4e-7 of that; one chain over K has 7.1e-7 at 2 x 128 tokens and 7.7e-7 at
+    320 + 192)."""
+    import torch
+    from perf import cases as C
+    case = dict(kind="encode", lens=",".join(map(str, lens)), layers=2, dtype="f32", weights="dtype", qk_norm=1,
+                layout=0, prefix=0)
+    errs = []
+    for seed in range(1, 5):
+        s = C.prepare(case, seed)
+        got, ref = C.run(s)["hidden"].double(), C.exact(case, seed)["hidden"]
+        errs.append(((got - ref).norm() / ref.norm()).item())
+        torch.cuda.synchronize()
+        s["enc"].close()
+    assert sum(errs) / len(errs) <= 4.6e-7, errs
