@@ -7,8 +7,8 @@
 namespace mte {
 
 static const TileCfg kTiles[] = {
-#define MTE_TILE_INFO(id, bm, bn, wm, wn, p, occ, f32, w8, su, tu, su8, tu8) \
-  {bm, bn, wm, wn, p, occ, f32, w8, su, tu, su8, tu8},
+#define MTE_TILE_INFO(id, bm, bn, wm, wn, p, occ, f32, w8, su, tu, su8, tu8, su32, tu32) \
+  {bm, bn, wm, wn, p, occ, f32, w8, {su32, su, su8}, {tu32, tu, tu8}},
     MTE_TILE_TABLE(MTE_TILE_INFO)
 #undef MTE_TILE_INFO
 };
@@ -76,7 +76,8 @@ static Plan plan_model(int M, int N, int K, int esz, int epi, int col_align, siz
       const int64_t wgs = (int64_t)(N / t.bn) * ((M + t.bm - 1) / t.bm) * sp;
       const double stages = (double)K / sp * esz / kStageBytes;
       // (heads halved over two waves: 4% more, their exchange and second pass)
-      const double tile = w8 ? stages * t.stage_us_w8 + t.tile_us_w8 : stages * t.stage_us + t.tile_us;
+      const int mode = w8 ? MODE_F8W : esz == 4 ? MODE_F32 : MODE_F16;
+      const double tile = stages * t.stage_us[mode] + t.tile_us[mode];
       const double cost = 2.0 + tile_rounds(wgs, t.occ) * tile * (half_heads(id, sp > 1 ? EPI_PARTIAL : epi, col_align) ? 1.04 : 1.0) + add;
       if (cost < cost_min) {
         cost_min = cost;

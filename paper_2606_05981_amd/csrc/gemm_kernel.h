@@ -705,10 +705,10 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) __attribute__((amdgpu_waves_per_
 }
 
 // A tile configuration is a compile-time instantiation of k_gemm. stage_us,
-// tile_us, ..._w8: its measured costs, for the planner.
+// tile_us: its measured costs for the planner, by Mode (fp32, fp16, e4m3 weights).
 struct TileCfg {
   int bm, bn, wm, wn, p, occ, f32, w8;
-  double stage_us, tile_us, stage_us_w8, tile_us_w8;
+  double stage_us[3], tile_us[3];
 };
 
 template <int MODE, int BM, int BN, int WM, int WN, int P, int EPI, int OCC, int F32, int W8>
@@ -737,40 +737,48 @@ static hipError_t run(const GemmArgs &a, int splits, hipStream_t s) {
 // Tile table: id -> instantiation (bm, bn, wave layout wm x wn, LDS ring
 // stages, workgroups per CU, built for fp32 operands too, built for e4m3
 // weights too), then the planner's costs in us of one tile alone on its CU, per
-// 128-byte K stage and per tile (prologue, epilogue), for fp16 weights (also used
-// for fp32) and for e4m3. The LDS ring (p * (bm + bn) * 128 bytes, bn / 2 for
+// 128-byte K stage and per tile (prologue, epilogue): fp16 weights, e4m3 weights,
+// fp32. The LDS ring (p * (bm + bn) * 128 bytes, bn / 2 for
 // e4m3 weights) must fit 160 KB / occ. bm a multiple of 32 (V^T tiles).
-// The costs are a least-squares fit (relative error, 4-13% rms) of the planner's
-// model to a sweep of every tile on MI355X over the decoder's and the vision
-// tower's projections at 16 ... 10240 rows; over that sweep the tile the model
-// picks is 0.2% (e4m3: 2%) slower than the fastest on average. The 256x256 tile
-// spills in its loop with e4m3 weights (nine times slower).
+// The costs are least-squares fits (relative error) of the planner's model to
+// sweeps of every tile on MI355X at 16 ... 10240 rows (fp32: ... 4096); they rank
+// tiles and do not predict times. Over the decoder's projections at width 2048,
+// at width 1024 and the vision tower's the pick is 0.8%, 1.6% and 0.2% slower than
+// the fastest tile on average (e4m3 1.1%, fp32 1.1%), single ones up to 23% (e4m3 29%).
+// The model's time of an unsplit launch is 9-17% rms off (e4m3 7-15%, its 32x64
+// tile 33%; fp32 4-6%), and low where the epilogue's bytes count, which it has no
+// term for: the 10240-row output projection, 101 us, is put at 72. The
+// 256x256 tile spills in its loop with e4m3 weights (nine times slower).
+// fp32 products are bound by the fp32 MFMAs, a sixteenth of the fp16 rate: a stage
+// costs 2-5 times what it does in fp16, and how evenly the rows divide over the chip
+// decides. Planned with the fp16 costs, on four-wave tiles of 128x128, 128x64, 64x64
+// and 32x64 only, one layer at width 2048 took 522 us at 337 rows and 3333 at 4096;
+// on these tiles 358 and 3146.
 #define MTE_TILE_TABLE(X) \
-  X(0, 256, 256, 4, 2, 2, 1, 0, 0, 1.335, 10.86, 0.000, 0.00)  \
-  X(1, 192, 384, 2, 4, 2, 1, 0, 1, 1.309, 15.45, 1.250, 14.30) \
-  X(2, 224, 256, 2, 4, 2, 1, 0, 1, 1.216, 10.07, 1.594, 9.60)  \
-  X(3, 160, 256, 2, 4, 3, 1, 0, 1, 0.835, 8.18, 0.891, 7.67)   \
-  X(4, 128, 256, 4, 2, 3, 1, 0, 1, 0.754, 7.23, 0.857, 6.89)   \
-  X(5, 192, 256, 4, 2, 2, 1, 0, 1, 1.119, 8.73, 1.015, 8.91)   \
-  X(6, 192, 128, 4, 2, 4, 1, 0, 1, 0.593, 5.47, 0.635, 5.27)   \
-  X(7, 192, 128, 6, 1, 3, 1, 0, 1, 0.664, 5.86, 0.785, 5.36)   \
-  X(8, 128, 128, 4, 2, 4, 1, 0, 1, 0.461, 4.42, 0.459, 4.25)   \
-  X(9, 128, 128, 4, 1, 4, 1, 1, 1, 0.486, 4.62, 0.577, 4.13)   \
-  X(10, 96, 128, 2, 4, 4, 1, 0, 1, 0.385, 3.82, 0.313, 3.22)   \
-  X(11, 96, 128, 6, 1, 5, 1, 0, 1, 0.452, 4.32, 0.617, 3.91)   \
-  X(12, 96, 64, 2, 2, 8, 1, 0, 1, 0.271, 3.10, 0.276, 2.87)    \
-  X(13, 64, 128, 4, 1, 6, 1, 0, 1, 0.374, 3.63, 0.483, 3.16)   \
-  X(14, 128, 64, 4, 1, 6, 1, 1, 1, 0.326, 3.36, 0.393, 3.13)   \
-  X(15, 32, 128, 2, 2, 8, 1, 0, 1, 0.267, 2.62, 0.296, 2.30)   \
-  X(16, 64, 64, 2, 2, 8, 1, 1, 1, 0.211, 2.29, 0.209, 2.20)    \
-  X(17, 64, 32, 4, 1, 6, 2, 0, 1, 0.191, 1.40, 0.196, 1.40)    \
-  X(18, 32, 64, 2, 2, 6, 2, 1, 1, 0.196, 1.45, 0.190, 1.35)
-
+  X(0, 256, 256, 4, 2, 2, 1, 0, 0, 1.335, 10.86, 0.000, 0.00, 0.000, 0.00)             \
+  X(1, 192, 384, 2, 4, 2, 1, 0, 1, 1.309, 15.45, 1.250, 14.30, 0.000, 0.00)            \
+  X(2, 224, 256, 2, 4, 2, 1, 0, 1, 1.216, 10.07, 1.594, 9.60, 0.000, 0.00)             \
+  X(3, 160, 256, 2, 4, 3, 1, 0, 1, 0.835, 8.18, 0.891, 7.67, 0.000, 0.00)              \
+  X(4, 128, 256, 4, 2, 3, 1, 0, 1, 0.754, 7.23, 0.857, 6.89, 0.000, 0.00)              \
+  X(5, 192, 256, 4, 2, 2, 1, 0, 1, 1.119, 8.73, 1.015, 8.91, 0.000, 0.00)              \
+  X(6, 192, 128, 4, 2, 4, 1, 1, 1, 0.593, 5.47, 0.635, 5.27, 3.120, 5.47)              \
+  X(7, 192, 128, 6, 1, 3, 1, 0, 1, 0.664, 5.86, 0.785, 5.36, 0.000, 0.00)              \
+  X(8, 128, 128, 4, 2, 4, 1, 1, 1, 0.461, 4.42, 0.459, 4.25, 2.091, 4.19)              \
+  X(9, 128, 128, 4, 1, 4, 1, 0, 1, 0.486, 4.62, 0.577, 4.13, 0.000, 0.00)              \
+  X(10, 96, 128, 2, 4, 4, 1, 1, 1, 0.385, 3.82, 0.313, 3.22, 1.588, 2.66)              \
+  X(11, 96, 128, 6, 1, 5, 1, 0, 1, 0.452, 4.32, 0.617, 3.91, 0.000, 0.00)              \
+  X(12, 96, 64, 2, 2, 8, 1, 1, 1, 0.271, 3.10, 0.276, 2.87, 0.870, 2.49)               \
+  X(13, 64, 128, 4, 1, 6, 1, 0, 1, 0.374, 3.63, 0.483, 3.16, 0.000, 0.00)              \
+  X(14, 128, 64, 4, 1, 6, 1, 1, 1, 0.326, 3.36, 0.393, 3.13, 1.167, 3.59)              \
+  X(15, 32, 128, 2, 2, 8, 1, 1, 1, 0.267, 2.62, 0.296, 2.30, 0.624, 2.74)              \
+  X(16, 64, 64, 2, 2, 8, 1, 0, 1, 0.211, 2.29, 0.209, 2.20, 0.000, 0.00)               \
+  X(17, 64, 32, 4, 1, 6, 2, 0, 1, 0.191, 1.40, 0.196, 1.40, 0.000, 0.00)               \
+  X(18, 32, 64, 2, 2, 6, 2, 1, 1, 0.196, 1.45, 0.190, 1.35, 0.374, 1.15)
 
 template <int MODE, int EPI>
 static hipError_t run_id(int id, const GemmArgs &a, int splits, hipStream_t s) {
   switch (id) {
-#define MTE_TILE_CASE(idv, bm, bn, wm, wn, p, occ, f32, w8, su, tu, su8, tu8) \
+#define MTE_TILE_CASE(idv, bm, bn, wm, wn, p, occ, f32, w8, su, tu, su8, tu8, su32, tu32) \
   case idv: return run<MODE, bm, bn, wm, wn, p, EPI, occ, f32, w8>(a, splits, s);
     MTE_TILE_TABLE(MTE_TILE_CASE)
 #undef MTE_TILE_CASE

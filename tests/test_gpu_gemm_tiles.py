@@ -67,6 +67,26 @@ def test_fp32_rows(rows):
     assert rel_err(got, ref) <= 1e-4
 
 
+WIDE_F32 = W.Dims(n_layers=1, hidden=1024, n_q_heads=8, n_kv_heads=4, head_dim=128, ffn=3072, dtype="f32")
+
+
+@pytest.mark.parametrize("rows,qk_norm", [(1, 1), (33, 1), (161, 1), (257, 1), (400, 0), (400, 1), (513, 1),
+                                          (769, 1), (1537, 1), (2049, 0), (2049, 1)])
+def test_wide_fp32_rows(rows, qk_norm):
+    """fp32 at width 1024, heads of 128: the eight-wave tiles (192, 128 and 96 rows) and 32x128,
+    whole and split over K, whose QKV epilogue halves a head between two waves."""
+    dims = WIDE_F32.with_(qk_norm=qk_norm)
+    x, pos, lens, got = run_layer(dims, rows)
+    assert rel_err(got, O.layer_forward(x, pos, lens, layer_w(dims, 0), dims)) <= 1e-4
+
+
+@pytest.mark.parametrize("rows", [1025, 1537, 2049])
+def test_tiny_fp32_many_rows(rows):
+    """fp32 heads of 64 on the tiles of many rows (32x128, 96x128, 128x128, 128x64)."""
+    x, pos, lens, got = run_layer(TINY, rows)
+    assert rel_err(got, O.layer_forward(x, pos, lens, layer_w(TINY, 0), TINY)) <= 1e-4
+
+
 @pytest.mark.parametrize("lens", [(32,), (128, 128), (320, 192)])
 def test_fp32_sums_in_stages(lens):
     """The unsplit fp32 products sum K in stages of 32: the relative error of two layers and the
