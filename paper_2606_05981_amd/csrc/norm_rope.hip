@@ -259,11 +259,12 @@ hipError_t launch_first_norm(int in_fmt, int out_fmt, const void *in, float *cop
   return rmsnorm(in_fmt, out_fmt, in, copy_to, nullptr, 0, g, out, rows, D, eps, &r, s);
 }
 
-// h[r, c] += parts[0][r, c] + ... + parts[np-1][r, c], in that order.
+// h[r, c] += parts[0][r, c] + ... + parts[np-1][r, c], in that order. h may be a
+// caller's buffer: aligned like one float.
 __global__ __launch_bounds__(256) void k_resid_add(float *__restrict__ h, Parts pt, size_t n4) {
   const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
   if (i >= n4) return;
-  f32x4 v = ((const f32x4 *)h)[i];
+  f32x4 v = ((const f32x4u *)h)[i];
   f32x4 q[kMaxParts];
 #pragma unroll
   for (int k = 0; k < kMaxParts; ++k)
@@ -273,7 +274,7 @@ __global__ __launch_bounds__(256) void k_resid_add(float *__restrict__ h, Parts 
     if (k < pt.np)
 #pragma unroll
       for (int e = 0; e < 4; ++e) v[e] += q[k][e];
-  ((f32x4 *)h)[i] = v;
+  ((f32x4u *)h)[i] = v;
 }
 
 hipError_t launch_resid_add(float *h, const float *parts, int nparts, int rows, int D, hipStream_t s) {
