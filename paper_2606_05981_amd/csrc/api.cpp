@@ -67,6 +67,15 @@ size_t qkv_bytes(const mte_config &c, size_t T) {
   const size_t rows = T * (c.n_q_heads + 2 * (size_t)c.n_kv_heads) * c.head_dim * 4;
   return c.dtype == MTE_F32 ? rows : std::max(rows, qk_bytes(c, T) + vt_bytes(c, T));
 }
+// Floats that the K-split partial sums of a batch of T tokens may take: 8 splits
+// of up to 256 rows of the widest product, or 2 of up to 2048 (narrower products
+// may be split further). A bound of the batch, not of the encoder's capacity, so
+// that a batch gets the same launch plan whatever max_tokens is.
+size_t split_elems(const mte_config &c, size_t T) {
+  const size_t nqkv = (c.n_q_heads + 2 * (size_t)c.n_kv_heads) * c.head_dim;
+  return std::max(8 * std::min<size_t>(T, 256), 2 * std::min<size_t>(T, 2048)) *
+         std::max(std::max(nqkv, 2 * (size_t)c.ffn), (size_t)c.hidden);
+}
 
 }  // namespace
 
@@ -301,11 +310,9 @@ int mte_encoder_create(const mte_config *cfg, const mte_weights *w, hipStream_t 
       hipMalloc(&wk.attn, MT * Hq * d * es) != hipSuccess ||
       hipMalloc(&wk.act, MT * F * es) != hipSuccess)
     return fail(MTE_E_OOM);
-  // K splits are planned for at most 8 splits of up to 256 rows, or 2 of up to 2048.
   wk.qk = (f16 *)wk.qkv;
   wk.vt = (f16 *)((char *)wk.qkv + qk_bytes(c, MT));
-  wk.ws_elems = std::max(8 * std::min<size_t>(MT, 256), 2 * std::min<size_t>(MT, 2048)) *
-                std::max(std::max(nqkv, 2 * F), D);
+  wk.ws_elems = split_elems(c, MT);
   if (hipMalloc((void **)&wk.ws, wk.ws_elems * sizeof(float)) != hipSuccess ||
       hipMalloc((void **)&wk.rcos, MT * (d / 2) * sizeof(float)) != hipSuccess ||
       hipMalloc((void **)&wk.rsin, MT * (d / 2) * sizeof(float)) != hipSuccess)
@@ -518,7 +525,7 @@ hipError_t run_layers(mte_encoder *e, const Work &wk, float *h, const int32_t *c
   const int nqkv = (Hq + 2 * Hkv) * d;
   const int mode = e->mode, gm = e->gmode, af = e->act_fmt;
   float *ws = wk.ws;
-  const size_t wn = wk.ws_elems;
+  const size_t wn = std::min(wk.ws_elems, split_elems(c, T));
   // `*pending` counts the partial sums of a K-split residual projection
   // still in ws, to be added into h by the next RMSNorm.
   int np = *pending;
@@ -703,11 +710,11 @@ int mte_encode_static(mte_encoder *e, const void *embeds, const int32_t *pos_thw
   wk.act = ptr[4];
   wk.rcos = (float *)ptr[5];
   wk.rsin = (float *)ptr[6];
-  // the encoder's own bound as well, so that a batch gets the same launch plan
-  // (hence bit-identical results) as through mte_encode whenever its partial
-  // sums fit here
+  // (run_layers bounds the splits by the batch as well, so that it gets the same
+  // launch plan, hence bit-identical results, as through mte_encode whenever its
+  // partial sums fit here)
   wk.ws = (float *)(base + off);
-  wk.ws_elems = std::min(((size_t)MTE_STATIC_SCRATCH_BYTES - off) / sizeof(float), e->w.ws_elems);
+  wk.ws_elems = ((size_t)MTE_STATIC_SCRATCH_BYTES - off) / sizeof(float);
   return encode_on(e, wk, embeds, pos_thw, cu, batch, T, out_hidden, stream) == hipSuccess ? MTE_OK : MTE_E_HIP;
 }
 
