@@ -1,8 +1,9 @@
 """The launch that opens a forward (first RMSNorm and rotary table together; it also writes the
-output residual stream of encode_layers) and the register-resident norm at every vector width:
-hidden sizes of 1, 2, 3, 5, 6, 7 (the general kernel), 8 and 10 times 256, fp32, two layers and
-the final norm against the oracle at 1e-4; and encode_layers in place, out of place and on
-buffers aligned like one float only, bit for bit the same."""
+residual stream where the input is the embeddings) and the register-resident norm at every vector
+width: hidden sizes of 1, 2, 3, 5, 6, 7 (the general kernel), 8 and 10 times 256, two layers and
+the final norm against the oracle, fp32 at 1e-4 and bf16 (bf16 rows in, fp16 out) at 3e-2; and
+encode_layers, whose first output projection reads the input rows as its residual, in place, out
+of place and on buffers aligned like one float only, bit for bit the same."""
 import sys
 
 import numpy as np
@@ -15,6 +16,24 @@ from tests.gpu_common import layout_tuples, make_encoder, oracle_encode, rel_err
 pytestmark = pytest.mark.gpu
 
 LAYOUTS = (W.SeqLayout(2, 1, 3, 4, 5), W.SeqLayout(0, 0, 0, 0, 1), W.SeqLayout(0, 1, 4, 4, 16))
+
+
+@pytest.mark.parametrize("n", [1, 2, 3, 5, 6, 7, 10, 12])
+def test_norm_widths_bf16(n):
+    import torch
+    from paper_2606_05981_amd.encoder import build_positions
+    assert torch.cuda.is_available(), "no GPU"
+    dims = W.DIMS_TINY.with_(hidden=256 * n, ffn=256, dtype="bf16")
+    emb = W.embeddings(dims, LAYOUTS)
+    print("hidden", dims.hidden, file=sys.stderr, flush=True)
+    enc = make_encoder(dims, max_tokens=64, max_batch=4, max_seq=64)
+    out = enc.encode(torch.from_numpy(emb).to("cuda", torch.bfloat16), build_positions(layout_tuples(LAYOUTS)),
+                     W.seq_lens(LAYOUTS))
+    torch.cuda.synchronize()
+    enc.close()
+    err = rel_err(out.cpu().numpy(), oracle_encode(dims, emb, LAYOUTS))
+    print("  err", err, file=sys.stderr, flush=True)
+    assert err <= 3e-2
 
 
 @pytest.mark.parametrize("n", [1, 2, 3, 5, 6, 7, 8, 10])

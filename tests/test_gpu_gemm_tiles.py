@@ -60,6 +60,27 @@ def test_e4m3_rows(rows):
     assert rel_err(got, ref) <= 1e-2
 
 
+@pytest.mark.parametrize("rows", [769, 1153, 1537, 2049, 2600])
+def test_e4m3_many_rows(rows):
+    """The e4m3 plans of large batches: whole products on the 96- to 192-row tiles, the down
+    projection split by two at 769 rows."""
+    x, pos, lens, got = run_layer(FULL, rows, weight_format=1)
+    ref = O.layer_forward(x, pos, lens, layer_w_e4m3(FULL, 0), FULL)
+    assert np.isfinite(got).all()
+    assert rel_err(got, ref) <= 1e-2
+
+
+@pytest.mark.parametrize("rows", [129, 769, 1153, 2049])
+def test_half_heads_without_qk_norm(rows):
+    """The QKV epilogue with half a 128-wide head per wave (32x128, 128x128, 192x128 and 160x256
+    tiles) and no QK-norm: rotation and operand layout without the exchange of the sums."""
+    dims = FULL.with_(qk_norm=0)
+    x, pos, lens, got = run_layer(dims, rows)
+    ref = O.layer_forward(x, pos, lens, layer_w(dims, 0), dims)
+    assert np.isfinite(got).all()
+    assert rel_err(got, ref) <= 1e-2
+
+
 @pytest.mark.parametrize("rows", [1, 31, 33, 65, 129, 700])
 def test_fp32_rows(rows):
     x, pos, lens, got = run_layer(TINY, rows)
@@ -87,12 +108,14 @@ def test_tiny_fp32_many_rows(rows):
     assert rel_err(got, O.layer_forward(x, pos, lens, layer_w(TINY, 0), TINY)) <= 1e-4
 
 
-@pytest.mark.parametrize("lens", [(32,), (128, 128), (320, 192)])
-def test_fp32_sums_in_stages(lens):
-    """The unsplit fp32 products sum K in stages of 32: the relative error of two layers and the
-    final norm against float64, averaged over four inputs, stays below 4.6e-7 (measured 3.6e-7,
-    4.2e-7 and 4.4e-7, single inputs within 0.4e-7 of that; one chain over K has 7.1e-7 at 2 x 128 tokens and 7.7e-7 at
-    320 + 192)."""
+@pytest.mark.parametrize("lens,bar", [((32,), 3.95e-7), ((128, 128), 4.75e-7), ((320, 192), 5.3e-7),
+                                      ((320,) * 4, 6.0e-7)])
+def test_fp32_sums_in_stages(lens, bar):
+    """The fp32 products sum K in stages of 32: the relative error of two layers and the final norm
+    against float64, averaged over four inputs, stays below the geometric middle of what the
+    kernels measure with stages and with one chain over each K range (same tiles and splits):
+    3.64e-7 and 4.34e-7 at 32 tokens, 4.07e-7 and 5.60e-7 at 2 x 128, 4.30e-7 and 6.58e-7 at
+    320 + 192, 4.39e-7 and 8.28e-7 at 4 x 320. Averages over other inputs differ by 0.2e-7."""
     import torch
     from perf import cases as C
     case = dict(kind="encode", lens=",".join(map(str, lens)), layers=2, dtype="f32", weights="dtype", qk_norm=1,
@@ -104,4 +127,4 @@ def test_fp32_sums_in_stages(lens):
         errs.append(((got - ref).norm() / ref.norm()).item())
         torch.cuda.synchronize()
         s["enc"].close()
-    assert sum(errs) / len(errs) <= 4.6e-7, errs
+    assert sum(errs) / len(errs) <= bar, errs

@@ -134,6 +134,23 @@ def test_vision_bf16_unaligned_patch_counts(torch):
         assert err <= TOL_SHORT
 
 
+@pytest.mark.parametrize("dtype,width,n,h,w", [("bf16", 256, 3, 64, 96), ("bf16", 1024, 4, 256, 256),
+                                               ("f32", 256, 3, 64, 96)])
+def test_vision_heads_of_128(torch, dtype, width, n, h, w):
+    """Heads of 128: the QKV epilogue with half a head per wave and a bias (32x128 tiles at 72
+    patches, 128x128 at 1024)."""
+    v = SV.VDIMS_FULL.with_(depth=1, hidden=width, n_heads=width // 128, head_dim=128, ffn=512, out_hidden=256,
+                            dtype=dtype)
+    img = SV.images(v, n, h, w)
+    _say("vision heads of 128", dtype, width, n, h, w)
+    enc = _encoder(v)
+    got = _run(torch, enc, v, img)
+    enc.close()
+    err = rel_err(got, _oracle(v, img))
+    _say("  err", err)
+    assert err <= (TOL_SHORT if dtype == "bf16" else TOL_F32)
+
+
 def test_vision_bf16_full_depth(torch):
     v = SV.VDIMS_FULL
     img = SV.images(v, 1, 256, 256)
