@@ -516,7 +516,9 @@ struct PrefixCtx {
 // Runs layers [l0, l1) on the fp32 residual stream `h` (T rows). The first
 // layer's attention norm is the caller's (launch_first_norm into wk.xn). h_in:
 // the stream's rows before the first layer where they are not in h yet (that
-// layer's output projection reads them there and writes h), or null.
+// layer's output projection reads them there and writes h), or null. *pending (out):
+// partial sums of the last down projection still in wk.ws, for the caller to add
+// into h.
 hipError_t run_layers(mte_encoder *e, const Work &wk, float *h, const int32_t *cu, int batch, int T, int l0,
                       int l1, int *pending, hipStream_t s,
                       const PrefixCtx *pre = nullptr, const float *h_in = nullptr) {
@@ -526,9 +528,7 @@ hipError_t run_layers(mte_encoder *e, const Work &wk, float *h, const int32_t *c
   const int mode = e->mode, gm = e->gmode, af = e->act_fmt;
   float *ws = wk.ws;
   const size_t wn = std::min(wk.ws_elems, split_elems(c, T));
-  // `*pending` counts the partial sums of a K-split residual projection
-  // still in ws, to be added into h by the next RMSNorm.
-  int np = *pending;
+  int np = 0;   // partial sums of a K-split residual projection still in ws, added into h by the next RMSNorm
   hipError_t err = hipSuccess;
 #define MTE_TRY(x) do { err = (x); if (err != hipSuccess) return err; } while (0)
   for (int l = l0; l < l1; ++l) {

@@ -8,7 +8,6 @@ namespace mte {
 
 typedef __bf16 bf16;
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef _Float16 f16;
 typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
@@ -30,17 +29,13 @@ template <> __device__ __forceinline__ bf16 from_f32<bf16>(float x) { return (bf
 // float -> fp16 rounds to nearest, ties to even (v_cvt_f16_f32).
 template <> __device__ __forceinline__ f16 from_f32<f16>(float x) { return (f16)x; }
 
-// A 16-byte per-lane MFMA operand fragment. For bf16 / fp16 it is one
-// v_mfma_f32_32x32x16_{bf16,f16} operand (8 values, k-extent 16); for f32 it is four
+// A 16-byte per-lane MFMA operand fragment. In the 32x32 forms (attention) it is
+// for fp16 one v_mfma_f32_32x32x16_f16 operand (8 values, k-extent 16), for f32 four
 // v_mfma_f32_32x32x2_f32 operands (one value each, k-extent 8 in total).
 // In both cases lane l supplies row (l % 32) and k-slot group (l / 32); A and
 // B fragments use the same (group, element) -> k assignment, so the dot
 // product is over the same k set whatever order the hardware sums it in.
 template <typename T> struct Frag;
-template <> struct Frag<bf16> {
-  typedef bf16x8 type;
-  static constexpr int kElems = 8;
-};
 template <> struct Frag<f16> {
   typedef f16x8 type;
   static constexpr int kElems = 8;
@@ -50,9 +45,6 @@ template <> struct Frag<float> {
   static constexpr int kElems = 4;
 };
 
-__device__ __forceinline__ void mfma32(f32x16 &acc, const bf16x8 &a, const bf16x8 &b) {
-  acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, acc, 0, 0, 0);
-}
 __device__ __forceinline__ void mfma32(f32x16 &acc, const f16x8 &a, const f16x8 &b) {
   acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, acc, 0, 0, 0);
 }
@@ -63,7 +55,7 @@ __device__ __forceinline__ void mfma32(f32x16 &acc, const f32x4 &a, const f32x4 
   acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[3], b[3], acc, 0, 0, 0);
 }
 
-// The 16x16 forms: lane l supplies row l % 16 and k-slot group l / 16 (fp16: one
+// The 16x16 forms (projections): lane l supplies row l % 16 and k-slot group l / 16 (fp16: one
 // v_mfma_f32_16x16x32_f16, k-extent 32; f32: four v_mfma_f32_16x16x4_f32, k-extent
 // 16 in total); register r of lane l of the accumulator holds row 4 (l / 16) + r,
 // column l % 16.

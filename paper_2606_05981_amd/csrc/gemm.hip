@@ -14,8 +14,6 @@ static const TileCfg kTiles[] = {
 };
 constexpr int kNumTiles = sizeof(kTiles) / sizeof(kTiles[0]);
 
-int gemm_num_tiles() { return kNumTiles; }
-
 // QKV on tile `id` with two waves of 64 columns per 128-wide head.
 static bool half_heads(int id, int epi, int col_align) {
   const TileCfg &t = kTiles[id];

@@ -87,17 +87,6 @@ struct GemmArgs {
   int gm, gn, gh;
 };
 
-// tanh-approximated GELU, 0.5 z (1 + tanh(u)) with u = sqrt(2/pi) (z + 0.044715 z^3),
-// evaluated as z * sigmoid(2u) = z / (1 + exp(-2u)) (the same function): one
-// exp and one hardware reciprocal (1 ulp) instead of a library tanh. Large
-// negative z: exp overflows to inf and the result is 0.
-__device__ __forceinline__ float gelu_tanh(float z) {
-  const float m2u = -1.5957691216057308f * z * (1.f + 0.044715f * z * z);
-  return z * __builtin_amdgcn_rcpf(1.f + __expf(m2u));
-}
-// silu(z) = z / (1 + exp(-z)), with the hardware reciprocal.
-__device__ __forceinline__ float silu_f(float z) { return z * __builtin_amdgcn_rcpf(1.f + __expf(-z)); }
-
 // Chunk swizzles for rows of 128 bytes (8 chunks) and 64 bytes (4 chunks),
 // functions of r % 16. A fragment read takes 16 rows at two logical chunks c and
 // c + 1 per half-wave, and the LDS serves a 16-byte read in groups of 16 lanes
@@ -408,10 +397,11 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) __attribute__((amdgpu_waves_per_
     for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
   // fp32 operands: the products of one stage (32 of K) are summed by themselves in
   // `part` and then added to acc, so that a sum over K rounds K / 32 times at its
-  // full size, not K / 4 times. Unsplit products then keep the precision that 8 K
-  // splits give (two 256-wide layers against float64, mean over 8 inputs: 32 tokens
-  // 3.61e-7 and 2 x 128 tokens 4.15e-7; one chain 4.35e-7 and 7.11e-7; 8 splits
-  // 3.74e-7 and 4.35e-7).
+  // full size, not K / 4 times (two 256-wide layers against float64, mean over 12
+  // inputs, same tiles and splits: 32 tokens 3.7e-7 against 4.5e-7 with one chain, 2 x
+  // 128 tokens 4.1e-7 against 5.7e-7, 8 x 320 tokens 4.4e-7 against 8.8e-7). Adding a
+  // tile's sum while later tiles' MFMAs run was slower (128x128 tile of four waves, 64
+  // stages: 142 us against 135).
   constexpr bool STAGED = MODE == MODE_F32;
   f32x4 part[STAGED ? TM : 1][STAGED ? TN : 1];
   if constexpr (STAGED) {
@@ -645,7 +635,10 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) __attribute__((amdgpu_waves_per_
     return;
   }
   if constexpr (EPI == EPI_GELU) {
-    // gelu_tanh(scale*a) * out_scale = a / (1 + 2^(c0 a (1 + k2 a^2))) * (scale * out_scale),
+    // tanh-approximated GELU: 0.5 z (1 + tanh(u)) with u = sqrt(2/pi) (z + 0.044715 z^3) is
+    // z / (1 + exp(-2u)), one exp and one hardware reciprocal instead of a library tanh
+    // (large negative z: exp overflows to inf and the result is 0). With z = scale * a,
+    //   gelu(z) * out_scale = a / (1 + 2^(c0 a (1 + k2 a^2))) * (scale * out_scale),
     // c0 = -2 sqrt(2/pi) log2(e) scale, k2 = 0.044715 scale^2.
     const float k2 = 0.044715f * g.scale * g.scale;
     const float c0 = -1.5957691216057308f * 1.4426950408889634f * g.scale;
@@ -719,7 +712,7 @@ static hipError_t run(const GemmArgs &a, int splits, hipStream_t s) {
     return hipErrorInvalidValue;  // gate/up pairs within a wave
   } else if constexpr (MODE == MODE_F32 && !F32) {
     return hipErrorInvalidValue;  // fp32 operands are built for a few tiles only
-  } else if constexpr (MODE == MODE_F8W && (!W8 || EPI == EPI_GELU)) {
+  } else if constexpr (MODE == MODE_F8W && (!W8 || EPI == EPI_GELU || EPI == EPI_STORE)) {
     return hipErrorInvalidValue;  // e4m3 weights: not every tile, decoder epilogues
   } else {
     constexpr int lds_bytes = P * (BM + (MODE == MODE_F8W ? BN / 2 : BN)) * kStageBytes;

@@ -89,14 +89,13 @@ hipError_t launch_gemm(int mode, int epi, const void *A, const void *W, void *C,
 
 // The same with an explicit tile configuration (index into the GEMM tile
 // table) and number of K splits (> 1 only with EPI_PARTIAL, partial sums
-// c_plane elements apart); used for tuning. Returns hipErrorInvalidValue if
-// the tile does not fit the shape.
+// c_plane elements apart): launch_gemm with its choice made. Returns
+// hipErrorInvalidValue if the tile does not fit the shape.
 hipError_t launch_gemm_tile(int mode, int epi, int tile, int splits, const void *A, const void *W,
                             void *C, size_t c_plane, int M, int N, int K, int ldc, float scale,
                             float out_scale, const QkvEpi *qe, hipStream_t s,
                             const float *col_scale = nullptr, const float *bias = nullptr,
-                       const float *resid = nullptr);
-int gemm_num_tiles();
+                            const float *resid = nullptr);
 
 // Per-row RMSNorm: out[r, :] = x[r, :] / sqrt(mean(x[r,:]^2) + eps) * g with
 // x = in + parts[0] + ... + parts[nparts-1] (float [rows, D] partial sums,
