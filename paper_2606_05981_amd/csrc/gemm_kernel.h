@@ -25,8 +25,8 @@
 // operands these GEMMs run at the card's power limit, and per flop the 16x16
 // form moves a quarter of the accumulator and twice the operand values
 // through the register file. Measured with no memory traffic (eight waves a
-// CU, random fp16 operands): 1.88 PFLOP/s with 16x16x32 against 1.60 with
-// 32x32x16 (both 2.40 on zeros, where power does not limit).
+// CU, random fp16 operands): 1.86 PFLOP/s with 16x16x32 against 1.69 with
+// 32x32x16 (2.37 and 2.42 on zeros, where power does not limit).
 //
 // Each workgroup (4, 6 or 8 waves, WM x WN) owns a BM x BN output tile; each
 // wave a (BM/WM) x (BN/WN) block of 16x16 MFMA tiles. Eight waves, or two
