@@ -58,6 +58,13 @@ static double tile_rounds(int64_t wgs, int occ) {
 // decide at every row count between the measured ones too (10240 rows of a
 // 2048-wide product: 223 us on 160x256 tiles, two whole rounds, against 291 on
 // 256x256, 1.25 rounds).
+// Splitting an fp32 product into single K stages has to be modelled 4% faster (the
+// model is 4-6% off there) than the shallower split: the stages are then only added
+// up one after the other by the consumer, which rounds more often at full size. Two
+// 256-wide layers against float64, 55 ... 176 tokens: 1.5% larger error on average where the
+// QKV product was split by 8 and not by 4 for a gain of less than that.
+constexpr double kSingleStageGain = 0.04;
+
 struct Plan {
   int tile, splits;
 };
@@ -77,7 +84,8 @@ static Plan plan_model(int M, int N, int K, int esz, int epi, int col_align, siz
       const int mode = w8 ? MODE_F8W : esz == 4 ? MODE_F32 : MODE_F16;
       const double tile = stages * t.stage_us[mode] + t.tile_us[mode];
       const double cost = 2.0 + tile_rounds(wgs, t.occ) * tile * (half_heads(id, sp > 1 ? EPI_PARTIAL : epi, col_align) ? 1.04 : 1.0) + add;
-      if (cost < cost_min) {
+      const bool single = esz == 4 && sp > best.splits && K / sp * esz == kStageBytes;
+      if (cost < cost_min * (single ? 1.0 - kSingleStageGain : 1.0)) {
         cost_min = cost;
         best = Plan{id, sp};
       }

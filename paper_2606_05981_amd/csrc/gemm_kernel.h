@@ -398,7 +398,7 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) __attribute__((amdgpu_waves_per_
   // fp32 operands: the products of one stage (32 of K) are summed by themselves in
   // `part` and then added to acc, so that a sum over K rounds K / 32 times at its
   // full size, not K / 4 times (two 256-wide layers against float64, mean over 12
-  // inputs, same tiles and splits: 32 tokens 3.7e-7 against 4.5e-7 with one chain, 2 x
+  // inputs, same tiles and splits: 32 tokens 3.6e-7 against 4.7e-7 with one chain, 2 x
   // 128 tokens 4.1e-7 against 5.7e-7, 8 x 320 tokens 4.4e-7 against 8.8e-7). Adding a
   // tile's sum while later tiles' MFMAs run was slower (128x128 tile of four waves, 64
   // stages: 142 us against 135).

@@ -108,13 +108,13 @@ def test_tiny_fp32_many_rows(rows):
     assert rel_err(got, O.layer_forward(x, pos, lens, layer_w(TINY, 0), TINY)) <= 1e-4
 
 
-@pytest.mark.parametrize("lens,bar", [((32,), 3.95e-7), ((128, 128), 4.75e-7), ((320, 192), 5.3e-7),
+@pytest.mark.parametrize("lens,bar", [((32,), 4.1e-7), ((128, 128), 4.75e-7), ((320, 192), 5.3e-7),
                                       ((320,) * 4, 6.0e-7)])
 def test_fp32_sums_in_stages(lens, bar):
     """The fp32 products sum K in stages of 32: the relative error of two layers and the final norm
     against float64, averaged over four inputs, stays below the geometric middle of what the
     kernels measure with stages and with one chain over each K range (same tiles and splits):
-    3.64e-7 and 4.34e-7 at 32 tokens, 4.07e-7 and 5.60e-7 at 2 x 128, 4.30e-7 and 6.58e-7 at
+    3.58e-7 and 4.76e-7 at 32 tokens, 4.07e-7 and 5.60e-7 at 2 x 128, 4.30e-7 and 6.58e-7 at
     320 + 192, 4.39e-7 and 8.28e-7 at 4 x 320. Averages over other inputs differ by 0.2e-7."""
     import torch
     from perf import cases as C
